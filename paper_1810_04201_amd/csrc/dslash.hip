@@ -20,11 +20,8 @@
 // coalesced 16-byte loads from the structure-of-arrays planes.
 #include <cstdlib>
 
-#include "device.hpp"
+#include "hops.hpp"
 
-#ifndef WD_XCD_REMAP
-#define WD_XCD_REMAP 1
-#endif
 // hops per scheduling group (see k_dslash): with two marching workgroups
 // per CU, float64 groups of 3 measured 1-2% faster than 1 (2 and 6 within
 // 0.3% of 3)
@@ -69,71 +66,6 @@
 
 namespace wd {
 
-template <int MU, int S, typename R>
-__device__ __forceinline__ void project(const cx<R> p[12], cx<R> h0[3], cx<R> h1[3]) {
-    // p[3*spin + colour]
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const cx<R> a0 = p[c], a1 = p[3 + c], a2 = p[6 + c], a3 = p[9 + c];
-        if (MU == 0) {
-            h0[c] = S > 0 ? a0 + times_i(a3) : a0 - times_i(a3);
-            h1[c] = S > 0 ? a1 + times_i(a2) : a1 - times_i(a2);
-        } else if (MU == 1) {
-            h0[c] = S > 0 ? a0 - a3 : a0 + a3;
-            h1[c] = S > 0 ? a1 + a2 : a1 - a2;
-        } else if (MU == 2) {
-            h0[c] = S > 0 ? a0 + times_i(a2) : a0 - times_i(a2);
-            h1[c] = S > 0 ? a1 - times_i(a3) : a1 + times_i(a3);
-        } else {
-            h0[c] = S > 0 ? a0 + a2 : a0 - a2;
-            h1[c] = S > 0 ? a1 + a3 : a1 - a3;
-        }
-    }
-}
-
-template <int MU, int S, typename R>
-__device__ __forceinline__ void accumulate(const cx<R> w0[3], const cx<R> w1[3], cx<R> acc[12]) {
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        acc[c] = acc[c] + w0[c];
-        acc[3 + c] = acc[3 + c] + w1[c];
-        if (MU == 0) {
-            // lower: -s i w1, -s i w0
-            acc[6 + c] = S > 0 ? acc[6 + c] - times_i(w1[c]) : acc[6 + c] + times_i(w1[c]);
-            acc[9 + c] = S > 0 ? acc[9 + c] - times_i(w0[c]) : acc[9 + c] + times_i(w0[c]);
-        } else if (MU == 1) {
-            // lower: s w1, -s w0
-            acc[6 + c] = S > 0 ? acc[6 + c] + w1[c] : acc[6 + c] - w1[c];
-            acc[9 + c] = S > 0 ? acc[9 + c] - w0[c] : acc[9 + c] + w0[c];
-        } else if (MU == 2) {
-            // lower: -s i w0, s i w1
-            acc[6 + c] = S > 0 ? acc[6 + c] - times_i(w0[c]) : acc[6 + c] + times_i(w0[c]);
-            acc[9 + c] = S > 0 ? acc[9 + c] + times_i(w1[c]) : acc[9 + c] - times_i(w1[c]);
-        } else {
-            // lower: s w0, s w1
-            acc[6 + c] = S > 0 ? acc[6 + c] + w0[c] : acc[6 + c] - w0[c];
-            acc[9 + c] = S > 0 ? acc[9 + c] + w1[c] : acc[9 + c] - w1[c];
-        }
-    }
-}
-
-// w = U h  or  w = U^dag h
-template <bool ADJ, typename R>
-__device__ __forceinline__ void su3_mul(const cx<R> u[9], const cx<R> h[3], cx<R> w[3]) {
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        cx<R> s = {R(0), R(0)};
-#pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            if (ADJ)
-                s = cfmac(u[3 * b + a], h[b], s);  // conj(U[b][a]) h[b]
-            else
-                s = cfma(u[3 * a + b], h[b], s);   // U[a][b] h[b]
-        }
-        w[a] = s;
-    }
-}
-
 // one hop: project the neighbour spinor, multiply by the link, rebuild, add
 template <int MU, int S, bool BWD, int PREC, int LF = PREC>
 __device__ __forceinline__ void hop(const void *gauge, const FieldRef &in, int nbr_entry,
@@ -171,38 +103,6 @@ __device__ __forceinline__ void hop(const void *gauge, const FieldRef &in, int n
     }
     cx<R> u[9];
     Link<LF>::load(gauge, MU, link_site, u);
-    cx<R> w0[3], w1[3];
-    su3_mul<BWD>(u, h0, w0);
-    su3_mul<BWD>(u, h1, w1);
-    accumulate<MU, S>(w0, w1, acc);
-}
-
-// Workgroups are dealt round-robin to the 8 XCDs (each with its own L2).
-// With WD_XCD_REMAP each XCD instead walks one contiguous run of logical
-// blocks, so that neighbours within a few thousand sites share an L2.
-__device__ __forceinline__ int logical_block() {
-#if WD_XCD_REMAP
-    const int nb = gridDim.x, b = blockIdx.x;
-    const int x = b & 7, i = b >> 3;
-    const int q = nb >> 3, r = nb & 7;
-    return x * q + (x < r ? x : r) + i;
-#else
-    return blockIdx.x;
-#endif
-}
-
-// one hop with the neighbour spinor and the link already in registers
-template <int MU, int S, bool BWD, typename R>
-__device__ __forceinline__ void hop_p(const cx<R> p[12], const cx<R> u[9], bool negate,
-                                      cx<R> acc[12]) {
-    cx<R> h0[3], h1[3];
-    project<MU, S>(p, h0, h1);
-    const R sg = negate ? R(-1) : R(1);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        h0[c] = scale(sg, h0[c]);
-        h1[c] = scale(sg, h1[c]);
-    }
     cx<R> w0[3], w1[3];
     su3_mul<BWD>(u, h0, w0);
     su3_mul<BWD>(u, h1, w1);
@@ -310,7 +210,8 @@ __device__ __forceinline__ void hop_s(const void *gauge, const FieldRef &in, con
     accumulate<MU, S>(w0, w1, acc);
 }
 
-template <int PREC, bool DAG, bool RED, int GROUP, int LF = PREC>
+// COUT: the output goes to a canonical float64 field (out.data) instead.
+template <int PREC, bool DAG, bool RED, int GROUP, int LF = PREC, bool COUT = false>
 __global__ void __launch_bounds__(256) k_dslash(Geom g, const void *__restrict__ gauge, FieldRef in,
                                                 FieldRef out, double kappa_d, RedArgs red,
                                                 Gate gate) {
@@ -326,6 +227,10 @@ __global__ void __launch_bounds__(256) k_dslash(Geom g, const void *__restrict__
     if (!gate_rhs(gate, rhs)) return;  // workgroup-uniform
     const FieldRef fin = rhs_view(in, rhs);
     const int site = sb * blockDim.x + threadIdx.x;
+    __shared__ __align__(16) char stage[COUT ? kSiteBlock / 64 * Spinor<PREC>::kTileBytes : 16];
+    const FieldRef tile = lds_view(
+        fin, stage + (COUT ? (threadIdx.x >> 6) * Spinor<PREC>::kTileBytes : 0));
+    int64_t lex = -1;
     double nrm = 0.0;
     if (site < g.V) {
         const Nbrs nb = neighbours(g, site);
@@ -371,8 +276,16 @@ __global__ void __launch_bounds__(256) k_dslash(Geom g, const void *__restrict__
             c[k] = c[k] - scale(kappa, acc[k]);
             if (RED) nrm += (double)c[k].re * (double)c[k].re + (double)c[k].im * (double)c[k].im;
         }
-        Spinor<PREC>::store(rhs_view(out, rhs), site, c);
+        if constexpr (COUT) {
+            int x, y, z, t;
+            coords_of(g, site, x, y, z, t);
+            lex = (int64_t)rhs * g.V + lex_of(g, x, y, z, t);
+            Spinor<PREC>::store(tile, (int)(threadIdx.x & 63), c);
+        } else {
+            Spinor<PREC>::store(rhs_view(out, rhs), site, c);
+        }
     }
+    if constexpr (COUT) export_tile<PREC>((double2 *)out.data, lex, tile);
     if (RED) reduce_block(nrm, red.partials, (size_t)sb * nrhs + rhs);
 }
 
@@ -435,8 +348,9 @@ __device__ __forceinline__ double xr_site(const XrArgs &a, int rhs, int i,
 // never stored: r -= alpha q, and the reduction is |r|^2 (see XrArgs).  out
 // is unused.
 // LF: the link form (PREC's own, or F64-12 for float64).
+// COUT: the output goes to a canonical float64 field (out.data) instead.
 template <int PREC, bool DAG, bool RED, int GROUP, bool HALO = false, bool XR = false,
-          int LF = PREC>
+          int LF = PREC, bool COUT = false>
 __global__ void __launch_bounds__(kTmMaxBlock) k_dslash_tm(Geom g, const void *__restrict__ gauge,
                                                    FieldRef in, FieldRef out, double kappa_d,
                                                    RedArgs red, Gate gate, int tchunk,
@@ -623,7 +537,7 @@ __global__ void __launch_bounds__(kTmMaxBlock) k_dslash_tm(Geom g, const void *_
             nrm = xr_site_r<PREC>(xr, rhs, i, (R)gate.st[rhs].alpha, c, rpre);
         else if constexpr (XR)
             nrm = xr_site<PREC>(xr, rhs, i, (R)gate.st[rhs].alpha, c);
-        else
+        else if constexpr (!COUT)
             Spinor<PREC>::template store<WD_NT_OUT>(fout, i, c);
         if (RED) {
 #pragma unroll
@@ -631,6 +545,17 @@ __global__ void __launch_bounds__(kTmMaxBlock) k_dslash_tm(Geom g, const void *_
             if ((l & 63) == 0) wsum[odd][l >> 6] = nrm;
         }
         __syncthreads();  // the current image is free for the next copy
+        if constexpr (COUT) {
+            // out through this wave's tile of the image
+            int x, y, z, tt;
+            coords_of(g, i, x, y, z, tt);
+            FieldRef tile = cur;
+            tile.data = (char *)cur.data +
+                        __builtin_amdgcn_readfirstlane(l >> 6) * Spinor<PREC>::kTileBytes;
+            Spinor<PREC>::store(tile, l & 63, c);
+            export_tile<PREC>((double2 *)out.data, (int64_t)rhs * g.V + lex_of(g, x, y, z, tt),
+                              tile);
+        }
         if (RED && l == 0) {
             double s = 0.0;
             for (int w = 0; w < (wvol >> 6); ++w) s += wsum[odd][w];
@@ -766,6 +691,52 @@ void launch_dslash(const Geom &g, const void *gauge, double kappa, int dagger, F
             else
                 launch_prec<WD_F16>(g, gauge, kappa, dagger, in, out, red, gate, s, nullptr);
             break;
+    }
+}
+
+// the plain stencil with a canonical float64 output (float32, binary16)
+template <int PREC, bool DAG, int LF>
+static void launch_canon_out(const Geom &g, const void *gauge, double kappa, FieldRef in,
+                             FieldRef out, hipStream_t s) {
+    constexpr int G = HopGroup<PREC>::value;
+    const Gate none{nullptr, nullptr, GATE_ACTIVE};
+    if (tm_eligible(g) && tm_fits<PREC>(g) && !g_force_site_kernel) {
+        const int wvol = tm_wvol(g, PREC);
+        const int nsub = g.bvol / wvol;
+        const int tch = tm_chunk(g, in.nrhs * nsub);
+        const int ncols = g.V / (g.L[3] * g.bvol);
+        const dim3 grid(tm_blocks(g, tch) * nsub * in.nrhs), bs(wvol);
+        const size_t lds = 2 * slice_bytes<PREC>(wvol);
+        auto k = k_dslash_tm<PREC, DAG, false, G, false, false, LF, true>;
+        allow_lds(k, lds);
+        hipLaunchKernelGGL(k, grid, bs, lds, s, g, gauge, in, out, kappa, RedArgs{}, none, tch,
+                           ncols, Halo{nullptr, nullptr, nullptr, 0, 0, 0, 0, 1}, XrArgs{});
+        return;
+    }
+    hipLaunchKernelGGL((k_dslash<PREC, DAG, false, G, LF, true>),
+                       dim3(site_blocks(g.V) * in.nrhs), dim3(kSiteBlock), 0, s, g, gauge, in, out,
+                       kappa, RedArgs{}, none);
+}
+
+void launch_dslash_canon(const Geom &g, const void *gauge, double kappa, int dagger, FieldRef in,
+                         double *out, hipStream_t s) {
+    FieldRef o{};
+    o.data = out;
+    if (in.prec == WD_F32) {
+        if (dagger)
+            launch_canon_out<WD_F32, true, WD_F32>(g, gauge, kappa, in, o, s);
+        else
+            launch_canon_out<WD_F32, false, WD_F32>(g, gauge, kappa, in, o, s);
+    } else if (g.f16_links8) {
+        if (dagger)
+            launch_canon_out<WD_F16, true, kLinkF16R8>(g, gauge, kappa, in, o, s);
+        else
+            launch_canon_out<WD_F16, false, kLinkF16R8>(g, gauge, kappa, in, o, s);
+    } else {
+        if (dagger)
+            launch_canon_out<WD_F16, true, WD_F16>(g, gauge, kappa, in, o, s);
+        else
+            launch_canon_out<WD_F16, false, WD_F16>(g, gauge, kappa, in, o, s);
     }
 }
 

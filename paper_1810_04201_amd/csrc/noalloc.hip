@@ -1,7 +1,7 @@
 // wd_apply_noalloc: the operator application of wd_apply for callers that
 // cannot allocate device memory (code under HIP graph capture, tight serving
-// loops, harnesses that forbid allocation).  The two internal-layout fields
-// that wd_apply allocates stream-ordered live instead in a file-scope device
+// loops, harnesses that forbid allocation).  The internal-layout fields
+// that wd_apply may allocate stream-ordered live instead in a file-scope device
 // array of fixed size, one copy per GPU, held until the process ends.
 //
 // In host code `scratch` names a host-side stand-in, not device memory: its
@@ -81,17 +81,13 @@ extern "C" int wd_apply_noalloc(wd_lattice *lat, double kappa, int prec, int dag
     char *base = (char *)scratch_on_device(&err);
     if (!base) return err;
     hipStream_t s = (hipStream_t)stream;
-    char *cur = base;
-    FieldRef a = carve(cur, prec, nrhs, V);
-    cur = base + one;
-    FieldRef b = carve(cur, prec, nrhs, V);
-    // the kernels compute in - kappa' * (hops): the +kappa sign is kappa' = -kappa
-    const double k = -lat->hop_sign * kappa;
-    const void *g12 = prec == WD_F64 ? lat->gauge12 : nullptr;
-    launch_import(in, a, lat->g, s);
-    launch_dslash(lat->g, gauge, k, dagger, a, b, nullptr, Gate{nullptr, nullptr, GATE_ACTIVE}, s,
-                  g12);
-    launch_export(b, out, lat->g, s);
+    if (!apply_direct(lat, gauge, kappa, prec, dagger, nrhs, in, out, s)) {
+        char *cur = base;
+        FieldRef a = carve(cur, prec, nrhs, V), b{};
+        cur = base + one;
+        if (apply_needs_two(prec, out)) b = carve(cur, prec, nrhs, V);
+        apply_fields(lat, gauge, kappa, dagger, in, out, a, b, s);
+    }
     WD_LAUNCH_CHECK();
     return WD_OK;
 }

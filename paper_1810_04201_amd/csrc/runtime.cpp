@@ -233,15 +233,40 @@ static void timed(const char *name, hipStream_t s, F &&launch) {
     g_pending.push_back({name, a, b});
 }
 
+static const char *const kDslashNames[3] = {"dslash_f64", "dslash_f32", "dslash_f16"};
+
 void dslash(wd_lattice *lat, const void *gauge, double kappa, int dagger, const FieldRef &in,
             const FieldRef &out, const RedArgs *red, Gate gate, hipStream_t s) {
     // the kernels compute in - kappa' * (hops): the +kappa sign is kappa' = -kappa
     kappa = -lat->hop_sign * kappa;
-    static const char *names[3] = {"dslash_f64", "dslash_f32", "dslash_f16"};
     // float64 on the lattice's own links: the 12-real form where it exists
     const void *g12 = in.prec == WD_F64 && gauge == lat->gauge[WD_F64] ? lat->gauge12 : nullptr;
-    timed(names[in.prec], s,
+    timed(kDslashNames[in.prec], s,
           [&] { launch_dslash(lat->g, gauge, kappa, dagger, in, out, red, gate, s, g12); });
+}
+
+bool apply_direct(wd_lattice *lat, const void *gauge, double kappa, int prec, int dagger,
+                  int nrhs, const double *in, double *out, hipStream_t s) {
+    if (!apply_direct_ok(lat->g, prec, nrhs, in, out)) return false;
+    timed(kDslashNames[prec], s, [&] {
+        launch_apply(lat->g, gauge, prec == WD_F64 ? lat->gauge12 : nullptr,
+                     -lat->hop_sign * kappa, prec, dagger, nrhs, in, out, s);
+    });
+    return true;
+}
+
+void apply_fields(wd_lattice *lat, const void *gauge, double kappa, int dagger,
+                  const double *in, double *out, const FieldRef &a, const FieldRef &b,
+                  hipStream_t s) {
+    launch_import(in, a, lat->g, s);
+    if (!b.data) {
+        timed(kDslashNames[a.prec], s, [&] {
+            launch_dslash_canon(lat->g, gauge, -lat->hop_sign * kappa, dagger, a, out, s);
+        });
+        return;
+    }
+    dslash(lat, gauge, kappa, dagger, a, b, nullptr, Gate{nullptr, nullptr, GATE_ACTIVE}, s);
+    launch_export(b, out, lat->g, s);
 }
 
 bool dslash_xr(wd_lattice *lat, const void *gauge, double kappa, int dagger, const FieldRef &in,
@@ -507,20 +532,23 @@ int wd_apply(wd_lattice *lat, double kappa, int prec, int dagger, int nrhs, cons
     int err = WD_OK;
     void *g = gauge_for(lat, prec, s, &err);
     if (!g) return err;
+    if (apply_direct(lat, g, kappa, prec, dagger, nrhs, in, out, s)) {
+        WD_LAUNCH_CHECK();
+        return WD_OK;
+    }
     const int V = lat->g.V;
+    const bool two = apply_needs_two(prec, out);
     size_t one = field_data_bytes(prec, V, nrhs) + 256;
     void *mem = nullptr;
-    hipError_t he = hipMallocAsync(&mem, 2 * one, s);
+    hipError_t he = hipMallocAsync(&mem, (two ? 2 : 1) * one, s);
     if (he != hipSuccess)
-        return fail(WD_ERR_NOMEM, "workspace allocation of %zu bytes failed: %s", 2 * one,
-                    hipGetErrorString(he));
+        return fail(WD_ERR_NOMEM, "workspace allocation of %zu bytes failed: %s",
+                    (two ? 2 : 1) * one, hipGetErrorString(he));
     char *cur = (char *)mem;
-    FieldRef a = carve(cur, prec, nrhs, V);
+    FieldRef a = carve(cur, prec, nrhs, V), b{};
     cur = (char *)mem + one;
-    FieldRef b = carve(cur, prec, nrhs, V);
-    launch_import(in, a, lat->g, s);
-    dslash(lat, g, kappa, dagger, a, b, nullptr, Gate{nullptr, nullptr, GATE_ACTIVE}, s);
-    launch_export(b, out, lat->g, s);
+    if (two) b = carve(cur, prec, nrhs, V);
+    apply_fields(lat, g, kappa, dagger, in, out, a, b, s);
     (void)hipFreeAsync(mem, s);
     WD_LAUNCH_CHECK();
     return WD_OK;

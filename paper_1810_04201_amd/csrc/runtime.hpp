@@ -99,6 +99,21 @@ void hop_half_xr(wd_lattice *lat, void *const gh[2], int p, double kappa, double
 void dslash(wd_lattice *lat, const void *gauge, double kappa, int dagger, const FieldRef &in,
             const FieldRef &out, const RedArgs *red, Gate gate, hipStream_t s);
 
+// the operator on canonical spinors in one launch where there is such a form
+// (see launch_apply), with optional event timing; false: nothing launched
+bool apply_direct(wd_lattice *lat, const void *gauge, double kappa, int prec, int dagger,
+                  int nrhs, const double *in, double *out, hipStream_t s);
+// the operator on canonical spinors through internal fields: import into a,
+// then the stencil with a canonical output, or (b given) into b and an export
+void apply_fields(wd_lattice *lat, const void *gauge, double kappa, int dagger,
+                  const double *in, double *out, const FieldRef &a, const FieldRef &b,
+                  hipStream_t s);
+// the second form: float64 (only its misaligned buffers come here) and an
+// output off 16 bytes
+inline bool apply_needs_two(int prec, const double *out) {
+    return prec == WD_F64 || ((uintptr_t)out & 15) != 0;
+}
+
 // stencil launch fused with the CG update that consumes its output (see
 // launch_dslash_xr), with optional event timing; false if not supported
 bool dslash_xr(wd_lattice *lat, const void *gauge, double kappa, int dagger, const FieldRef &in,

@@ -589,6 +589,17 @@ void launch_accum_zero(FieldRef x64, FieldRef xlo, FieldRef p, Gate gate, hipStr
 void launch_dslash(const Geom &g, const void *gauge, double kappa, int dagger, FieldRef in,
                    FieldRef out, const RedArgs *red, Gate gate, hipStream_t s,
                    const void *g12 = nullptr);
+// out = D in (dagger 0) or D^dag in (dagger 1) on canonical float64 spinors
+// [rhs][V][24] in one pass: the same results, bit for bit, as an import,
+// launch_dslash and an export.  Only where apply_direct_ok: both pointers
+// 16-byte aligned; float64, and float32 on small lattices.
+bool apply_direct_ok(const Geom &g, int prec, int nrhs, const double *in, const double *out);
+void launch_apply(const Geom &g, const void *gauge, const void *g12, double kappa, int prec,
+                  int dagger, int nrhs, const double *in, double *out, hipStream_t s);
+// the same with a float32 or binary16 field as input: the stencil and the
+// export of its result in one pass (out 16-byte aligned)
+void launch_dslash_canon(const Geom &g, const void *gauge, double kappa, int dagger, FieldRef in,
+                         double *out, hipStream_t s);
 // q = D in (or D^dag in) consumed where it is formed: r -= alpha q, |r|^2
 // reduced with red.mode (RED_RR) and finalised; q is not stored.  Only the marching stencil does this: returns false (nothing
 // launched) where it does not run
