@@ -148,6 +148,32 @@ __device__ __forceinline__ void slice_copy(const FieldRef &f, int tile0, char *i
                                          (lds_void *)(dst + NP * 1024), 4, 0, 0);
 }
 
+// The same for a part that starts at any entry: lane l copies entry first + l
+// to place tid of the image (lanes past the part repeat its last entry).
+template <int PREC>
+__device__ __forceinline__ void slice_copy_ragged(const FieldRef &f, int entry, char *img) {
+    constexpr size_t TB = Spinor<PREC>::kTileBytes;
+    constexpr int NP = PREC == WD_F64 ? 12 : (PREC == WD_F32 ? 6 : 3);
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    char *dst = img + (size_t)w * TB;
+#pragma unroll
+    for (int k = 0; k < NP; ++k)
+        __builtin_amdgcn_global_load_lds((const void *)tile_elem(f.data, TB, entry, k),
+                                         (lds_void *)(dst + k * 1024), 16, 0, 0);
+    if constexpr (PREC == WD_F16)
+        __builtin_amdgcn_global_load_lds((const void *)Spinor<WD_F16>::scale_ptr(f, entry),
+                                         (lds_void *)(dst + NP * 1024), 4, 0, 0);
+}
+
+// Keeps a site's result where it is: a store that only some lanes do would
+// otherwise draw the whole step's arithmetic behind its branch, and every
+// operand would be spilled.
+template <typename R>
+__device__ __forceinline__ void pin(cx<R> v[12]) {
+#pragma unroll
+    for (int k = 0; k < 12; ++k) asm volatile("" : "+v"(v[k].re), "+v"(v[k].im));
+}
+
 // Wait until this wave's outstanding copies have landed in LDS.  Only this
 // wave reads its tiles before the barrier that ends the step, so no barrier is
 // needed here: with one, the waves of a workgroup met twice per slice and
@@ -297,7 +323,8 @@ template <int PREC>
 __device__ __forceinline__ double xr_site_r(const XrArgs &a, int rhs, int i,
                                             typename Spinor<PREC>::R alpha,
                                             const cx<typename Spinor<PREC>::R> q[12],
-                                            cx<typename Spinor<PREC>::R> v[12]) {
+                                            cx<typename Spinor<PREC>::R> v[12],
+                                            bool mine = true) {
     constexpr int PX = xr_prec_of(PREC);
     double nrm = 0.0;
 #pragma unroll
@@ -305,19 +332,20 @@ __device__ __forceinline__ double xr_site_r(const XrArgs &a, int rhs, int i,
         v[k] = {v[k].re - alpha * q[k].re, v[k].im - alpha * q[k].im};
         nrm += (double)v[k].re * (double)v[k].re + (double)v[k].im * (double)v[k].im;
     }
-    Spinor<PX>::template store<WD_NT_OUT>(rhs_view(a.r, rhs), i, v);
+    if (mine) Spinor<PX>::template store<WD_NT_OUT>(rhs_view(a.r, rhs), i, v);
     return nrm;
 }
 
 template <int PREC>
 __device__ __forceinline__ double xr_site(const XrArgs &a, int rhs, int i,
                                           typename Spinor<PREC>::R alpha,
-                                          const cx<typename Spinor<PREC>::R> q[12]) {
+                                          const cx<typename Spinor<PREC>::R> q[12],
+                                          bool mine = true) {
     constexpr int PX = xr_prec_of(PREC);
     using R = typename Spinor<PREC>::R;
     cx<R> v[12];
     Spinor<PX>::load(rhs_view(a.r, rhs), i, v);
-    return xr_site_r<PREC>(a, rhs, i, alpha, q, v);
+    return xr_site_r<PREC>(a, rhs, i, alpha, q, v, mine);
 }
 
 // Time-marching stencil.  One workgroup per brick column, chunk of time
@@ -349,12 +377,18 @@ __device__ __forceinline__ double xr_site(const XrArgs &a, int rhs, int i,
 // is unused.
 // LF: the link form (PREC's own, or F64-12 for float64).
 // COUT: the output goes to a canonical float64 field (out.data) instead.
+// RAG: the brick slice is no whole number of tiles; parts of w sites that
+// start anywhere, the last one shorter (see PartShape; without HALO).  Such
+// lattices took one lane per site before: 30^3 x 60 float64 520 -> 319 us,
+// float32 187 -> 148, binary16 95 -> 82, float64 CG iteration (with the fused
+// r update, which only this form has) 1584 -> 1033 us; 18^3 x 36 float64 69 ->
+// 43 us, CG iteration 212 -> 149.
 template <int PREC, bool DAG, bool RED, int GROUP, bool HALO = false, bool XR = false,
-          int LF = PREC, bool COUT = false>
+          int LF = PREC, bool COUT = false, bool RAG = false>
 __global__ void __launch_bounds__(kTmMaxBlock) k_dslash_tm(Geom g, const void *__restrict__ gauge,
                                                    FieldRef in, FieldRef out, double kappa_d,
                                                    RedArgs red, Gate gate, int tchunk,
-                                                   int ncols, Halo halo, XrArgs xr) {
+                                                   int ncols, int w, Halo halo, XrArgs xr) {
     using R = typename Spinor<PREC>::R;
     extern __shared__ __align__(16) char lds[];
     // wave sums of the step, double-buffered by its parity: wave 0 reads them
@@ -362,8 +396,7 @@ __global__ void __launch_bounds__(kTmMaxBlock) k_dslash_tm(Geom g, const void *_
     __shared__ double wsum[2][kTmMaxBlock / 64];
     if (gate_off(gate)) return;  // grid-uniform
     const int nrhs = in.nrhs;
-    const int wvol = (int)blockDim.x;  // sites of this workgroup's part of a slice
-    const int nsub = g.bvol / wvol;
+    const int nsub = RAG ? (g.bvol + w - 1) / w : g.bvol / w;
     const int lb = logical_block();
     const int cb = lb / nrhs;
     const int rhs = lb - cb * nrhs;
@@ -376,19 +409,23 @@ __global__ void __launch_bounds__(kTmMaxBlock) k_dslash_tm(Geom g, const void *_
     const int col = cc - lchunk * ncols;
     const int chunk = HALO ? halo.cfirst + lchunk * halo.cstep : lchunk;
     const int Lt = g.L[3], bvol = g.bvol;
-    const int l = (int)threadIdx.x;
+    const int tid = (int)threadIdx.x;
+    // sites of this workgroup's part of a slice; lanes past it repeat its last
+    const int wvol = RAG && bvol - h * w < w ? bvol - h * w : w;
+    const bool mine = !RAG || tid < wvol;
+    const int l = mine ? tid : wvol - 1;
     const int t0 = chunk * tchunk;
     const int t1 = t0 + tchunk < Lt ? t0 + tchunk : Lt;
     // first site of this workgroup's part of slice t: cbase + t * bvol
-    const int cbase = col * Lt * bvol + h * wvol;
+    const int cbase = col * Lt * bvol + h * w;
     char *img0 = lds;
-    char *img1 = lds + slice_bytes<PREC>(wvol);
+    char *img1 = lds + slice_bytes<PREC>((int)blockDim.x);
     constexpr int SF = DAG ? +1 : -1;
     constexpr int SB = -SF;
     const R kappa = (R)kappa_d;
 
     // halo: this workgroup's part of a face (first face site, staged views)
-    const int fbase = col * bvol + h * wvol;
+    const int fbase = col * bvol + h * w;
     FieldRef hprev = fin, hnext = fin;
     if (HALO) {
         hprev.data = (void *)halo.prev;
@@ -402,7 +439,10 @@ __global__ void __launch_bounds__(kTmMaxBlock) k_dslash_tm(Geom g, const void *_
     const bool prev_from_halo = HALO && t0 == 0;
 
     // prologue: slice t0 into image 0, and the backward t hop from t0 - 1
-    slice_copy<PREC>(fin, (cbase + t0 * bvol) >> 6, img0);
+    if constexpr (RAG)
+        slice_copy_ragged<PREC>(fin, cbase + t0 * bvol + l, img0);
+    else
+        slice_copy<PREC>(fin, (cbase + t0 * bvol) >> 6, img0);
     cx<R> cw0[3], cw1[3];
     {
         const int tprev = t0 == 0 ? Lt - 1 : t0 - 1;
@@ -442,8 +482,12 @@ __global__ void __launch_bounds__(kTmMaxBlock) k_dslash_tm(Geom g, const void *_
         const int tn = t + 1 < Lt ? t + 1 : 0;
         // the slice after the slab's last one is the staged next face
         const bool next_from_halo = HALO && t + 1 == Lt;
-        slice_copy<PREC>(next_from_halo ? hnext : fin,
-                         next_from_halo ? fbase >> 6 : (cbase + tn * bvol) >> 6, (char *)nxt.data);
+        if constexpr (RAG)
+            slice_copy_ragged<PREC>(fin, cbase + tn * bvol + l, (char *)nxt.data);
+        else
+            slice_copy<PREC>(next_from_halo ? hnext : fin,
+                             next_from_halo ? fbase >> 6 : (cbase + tn * bvol) >> 6,
+                             (char *)nxt.data);
         const int sbase = cbase + t * bvol;
         const int i = sbase + l;
         constexpr bool XPRE = XR && ((WD_XR_PREFETCH >> PREC) & 1);
@@ -533,16 +577,18 @@ __global__ void __launch_bounds__(kTmMaxBlock) k_dslash_tm(Geom g, const void *_
             if (RED && !XR)
                 nrm += (double)c[k].re * (double)c[k].re + (double)c[k].im * (double)c[k].im;
         }
+        if constexpr (RAG && XR) pin(c);
         if constexpr (XPRE)
-            nrm = xr_site_r<PREC>(xr, rhs, i, (R)gate.st[rhs].alpha, c, rpre);
+            nrm = xr_site_r<PREC>(xr, rhs, i, (R)gate.st[rhs].alpha, c, rpre, mine);
         else if constexpr (XR)
-            nrm = xr_site<PREC>(xr, rhs, i, (R)gate.st[rhs].alpha, c);
+            nrm = xr_site<PREC>(xr, rhs, i, (R)gate.st[rhs].alpha, c, mine);
         else if constexpr (!COUT)
             Spinor<PREC>::template store<WD_NT_OUT>(fout, i, c);
         if (RED) {
+            if (!mine) nrm = 0.0;
 #pragma unroll
             for (int off = 32; off > 0; off >>= 1) nrm += __shfl_xor(nrm, off, 64);
-            if ((l & 63) == 0) wsum[odd][l >> 6] = nrm;
+            if ((tid & 63) == 0) wsum[odd][tid >> 6] = nrm;
         }
         __syncthreads();  // the current image is free for the next copy
         if constexpr (COUT) {
@@ -551,14 +597,14 @@ __global__ void __launch_bounds__(kTmMaxBlock) k_dslash_tm(Geom g, const void *_
             coords_of(g, i, x, y, z, tt);
             FieldRef tile = cur;
             tile.data = (char *)cur.data +
-                        __builtin_amdgcn_readfirstlane(l >> 6) * Spinor<PREC>::kTileBytes;
-            Spinor<PREC>::store(tile, l & 63, c);
-            export_tile<PREC>((double2 *)out.data, (int64_t)rhs * g.V + lex_of(g, x, y, z, tt),
-                              tile);
+                        __builtin_amdgcn_readfirstlane(tid >> 6) * Spinor<PREC>::kTileBytes;
+            Spinor<PREC>::store(tile, tid & 63, c);
+            export_tile<PREC>((double2 *)out.data,
+                              mine ? (int64_t)rhs * g.V + lex_of(g, x, y, z, tt) : -1, tile);
         }
-        if (RED && l == 0) {
+        if (RED && tid == 0) {
             double s = 0.0;
-            for (int w = 0; w < (wvol >> 6); ++w) s += wsum[odd][w];
+            for (int v = 0; v < (int)(blockDim.x >> 6); ++v) s += wsum[odd][v];
             red.partials[(((size_t)col * Lt + t) * nsub + h) * nrhs + rhs] = s;
         }
     }
@@ -602,68 +648,85 @@ static void allow_lds(K kernel, size_t bytes) {
                                   (int)bytes);
 }
 
+// launch shape of a marching stencil over slices of n sites (entries)
+struct March {
+    PartShape p;
+    int tch, ncols, chunks;
+    dim3 grid, bs;
+    size_t lds;
+    bool ok;  // the form runs on this geometry
+};
+
 template <int PREC>
-static bool tm_fits(const Geom &g) {
+static March march_of(const Geom &g, int n, int nrhs) {
     static const size_t cap = max_lds_per_block();
-    return 2 * slice_bytes<PREC>(tm_wvol(g, PREC)) + 64 <= cap;
+    March m{};
+    if (!marches(n) || g_force_site_kernel) return m;
+    m.p = part_shape(n, PREC);
+    m.lds = 2 * slice_bytes<PREC>(m.p.threads);
+    m.ok = m.lds + 64 <= cap;
+    m.tch = tm_chunk(g, nrhs * m.p.nsub);
+    m.ncols = g.V / (g.L[3] * g.bvol);
+    m.chunks = (g.L[3] + m.tch - 1) / m.tch;
+    m.grid = dim3(m.ncols * m.chunks * m.p.nsub * nrhs);
+    m.bs = dim3(m.p.threads);
+    return m;
 }
 
-template <int PREC, bool DAG, bool RED, int LF = PREC>
-static void launch_tm_k(dim3 grid, dim3 bs, size_t lds, hipStream_t s, const Geom &g,
-                        const void *gauge, FieldRef in, FieldRef out, double kappa,
-                        const RedArgs &r, Gate gate, int tch, int ncols) {
+static const Halo kNoHalo{nullptr, nullptr, nullptr, 0, 0, 0, 0, 1};
+
+template <int PREC, bool DAG, bool RED, bool XR, int LF, bool COUT = false>
+static void launch_tm(const March &m, const Geom &g, const void *gauge, FieldRef in, FieldRef out,
+                      double kappa, const RedArgs &r, Gate gate, const XrArgs &xr,
+                      hipStream_t s) {
     constexpr int G = HopGroup<PREC>::value;
-    auto k = k_dslash_tm<PREC, DAG, RED, G, false, false, LF>;
-    allow_lds(k, lds);
-    hipLaunchKernelGGL(k, grid, bs, lds, s, g, gauge, in, out, kappa, r, gate, tch, ncols,
-                       Halo{nullptr, nullptr, nullptr, 0, 0, 0, 0, 1}, XrArgs{});
-}
-
-template <int PREC, int LF = PREC>
-static void launch_tm(const Geom &g, const void *gauge, double kappa, int dagger, FieldRef in,
-                      FieldRef out, const RedArgs *red, Gate gate, hipStream_t s) {
-    const int wvol = tm_wvol(g, PREC);
-    const int nsub = g.bvol / wvol;
-    const int tch = tm_chunk(g, in.nrhs * nsub);
-    const int ncols = g.V / (g.L[3] * g.bvol);
-    const dim3 grid(tm_blocks(g, tch) * nsub * in.nrhs), bs(wvol);
-    const size_t lds = 2 * slice_bytes<PREC>(wvol);
-    RedArgs r{};
-    if (red) r = *red;
-    if (dagger) {
-        if (red)
-            launch_tm_k<PREC, true, true, LF>(grid, bs, lds, s, g, gauge, in, out, kappa, r, gate, tch, ncols);
-        else
-            launch_tm_k<PREC, true, false, LF>(grid, bs, lds, s, g, gauge, in, out, kappa, r, gate, tch, ncols);
-    } else {
-        if (red)
-            launch_tm_k<PREC, false, true, LF>(grid, bs, lds, s, g, gauge, in, out, kappa, r, gate, tch, ncols);
-        else
-            launch_tm_k<PREC, false, false, LF>(grid, bs, lds, s, g, gauge, in, out, kappa, r, gate, tch, ncols);
-    }
-    // one partial per part of a brick slice: V / wvol of them per rhs
-    if (red) launch_finalize(r, g.V / wvol, gate.batch ? gate.mode : -1, s);
+    auto go = [&](auto k) {
+        allow_lds(k, m.lds);
+        hipLaunchKernelGGL(k, m.grid, m.bs, m.lds, s, g, gauge, in, out, kappa, r, gate, m.tch,
+                           m.ncols, m.p.w, kNoHalo, xr);
+    };
+    if (m.p.ragged)
+        go(k_dslash_tm<PREC, DAG, RED, G, false, XR, LF, COUT, true>);
+    else
+        go(k_dslash_tm<PREC, DAG, RED, G, false, XR, LF, COUT, false>);
 }
 
 template <int PREC, int LF = PREC>
 static void launch_prec(const Geom &g, const void *gauge, double kappa, int dagger, FieldRef in,
                         FieldRef out, const RedArgs *red, Gate gate, hipStream_t s,
                         const void *g12) {
-    // the marching stencil writes one partial per workgroup: use it only
-    // when the caller's partial buffer holds them (it always does when sized
-    // by reduce_partials_cap)
-    if (tm_eligible(g) && tm_fits<PREC>(g) && !g_force_site_kernel &&
-        (!red || (int64_t)(g.V / tm_wvol(g, PREC)) * in.nrhs <= red->partials_cap)) {
-        if (PREC == WD_F64 && g12)
-            launch_tm<WD_F64, kLinkF64R12>(g, g12, kappa, dagger, in, out, red, gate, s);
-        else
-            launch_tm<PREC, LF>(g, gauge, kappa, dagger, in, out, red, gate, s);
+    RedArgs r{};
+    if (red) r = *red;
+    // the marching stencil writes one partial per part of a slice: use it
+    // only when the caller's partial buffer holds them (it always does when
+    // sized by reduce_partials_cap)
+    March m = march_of<PREC>(g, g.bvol, in.nrhs);
+    if (PREC == WD_F16 && m.p.ragged && !red) m.ok = false;  // see launch_canon_out
+    if (m.ok && (!red || (int64_t)tm_partials(g, m.p) * in.nrhs <= red->partials_cap)) {
+        auto go = [&](auto lf, const void *links) {
+            constexpr int F = decltype(lf)::value;
+            if (dagger && red)
+                launch_tm<PREC, true, true, false, F>(m, g, links, in, out, kappa, r, gate, {}, s);
+            else if (dagger)
+                launch_tm<PREC, true, false, false, F>(m, g, links, in, out, kappa, r, gate, {}, s);
+            else if (red)
+                launch_tm<PREC, false, true, false, F>(m, g, links, in, out, kappa, r, gate, {}, s);
+            else
+                launch_tm<PREC, false, false, false, F>(m, g, links, in, out, kappa, r, gate, {}, s);
+        };
+        if constexpr (PREC == WD_F64) {
+            if (g12)
+                go(Int<kLinkF64R12>{}, g12);
+            else
+                go(Int<WD_F64>{}, gauge);
+        } else {
+            go(Int<LF>{}, gauge);
+        }
+        if (red) launch_finalize(r, tm_partials(g, m.p), gate.batch ? gate.mode : -1, s);
         return;
     }
     const int nb = site_blocks(g.V);
     const dim3 grid(nb * in.nrhs), bs(kSiteBlock);
-    RedArgs r{};
-    if (red) r = *red;
     constexpr int G = HopGroup<PREC>::value;
     if (dagger) {
         if (red)
@@ -700,17 +763,16 @@ static void launch_canon_out(const Geom &g, const void *gauge, double kappa, Fie
                              FieldRef out, hipStream_t s) {
     constexpr int G = HopGroup<PREC>::value;
     const Gate none{nullptr, nullptr, GATE_ACTIVE};
-    if (tm_eligible(g) && tm_fits<PREC>(g) && !g_force_site_kernel) {
-        const int wvol = tm_wvol(g, PREC);
-        const int nsub = g.bvol / wvol;
-        const int tch = tm_chunk(g, in.nrhs * nsub);
-        const int ncols = g.V / (g.L[3] * g.bvol);
-        const dim3 grid(tm_blocks(g, tch) * nsub * in.nrhs), bs(wvol);
-        const size_t lds = 2 * slice_bytes<PREC>(wvol);
-        auto k = k_dslash_tm<PREC, DAG, false, G, false, false, LF, true>;
-        allow_lds(k, lds);
-        hipLaunchKernelGGL(k, grid, bs, lds, s, g, gauge, in, out, kappa, RedArgs{}, none, tch,
-                           ncols, Halo{nullptr, nullptr, nullptr, 0, 0, 0, 0, 1}, XrArgs{});
+    // The marching binary16 stencil scales its carried t hop before it is
+    // summed, one lane per site while it is: the last binary16 bits differ.
+    // On slices that are no whole tiles a plain application keeps the form it
+    // always had (18^3 x 36, 2 rhs: 70.9 against 70.2 us); a solve's stencils
+    // march.
+    March m = march_of<PREC>(g, g.bvol, in.nrhs);
+    if (PREC == WD_F16 && m.p.ragged) m.ok = false;
+    if (m.ok) {
+        launch_tm<PREC, DAG, false, false, LF, true>(m, g, gauge, in, out, kappa, RedArgs{}, none,
+                                                     {}, s);
         return;
     }
     hipLaunchKernelGGL((k_dslash<PREC, DAG, false, G, LF, true>),
@@ -742,8 +804,8 @@ void launch_dslash_canon(const Geom &g, const void *gauge, double kappa, int dag
 
 template <int PREC>
 static bool xr_ok(const Geom &g, int nrhs, int partials_cap) {
-    return tm_eligible(g) && tm_fits<PREC>(g) && !g_force_site_kernel &&
-           (int64_t)(g.V / tm_wvol(g, PREC)) * nrhs <= partials_cap;
+    const March m = march_of<PREC>(g, g.bvol, nrhs);
+    return m.ok && (int64_t)tm_partials(g, m.p) * nrhs <= partials_cap;
 }
 
 bool dslash_xr_supported(const Geom &g, int prec, int nrhs, int partials_cap) {
@@ -758,26 +820,12 @@ template <int PREC, int LF = PREC>
 static bool xr_prec(const Geom &g, const void *gauge, double kappa, int dagger, FieldRef in,
                     const XrArgs &xr, const RedArgs &red, Gate gate, hipStream_t s) {
     if (!xr_ok<PREC>(g, in.nrhs, red.partials_cap)) return false;
-    const int wvol = tm_wvol(g, PREC);
-    const int nsub = g.bvol / wvol;
-    const int tch = tm_chunk(g, in.nrhs * nsub);
-    const int ncols = g.V / (g.L[3] * g.bvol);
-    const dim3 grid(tm_blocks(g, tch) * nsub * in.nrhs), bs(wvol);
-    const size_t lds = 2 * slice_bytes<PREC>(wvol);
-    constexpr int G = HopGroup<PREC>::value;
-    const Halo nh{nullptr, nullptr, nullptr, 0, 0, 0, 0, 1};
-    if (dagger) {
-        auto k = k_dslash_tm<PREC, true, true, G, false, true, LF>;
-        allow_lds(k, lds);
-        hipLaunchKernelGGL(k, grid, bs, lds, s, g, gauge, in, FieldRef{}, kappa, red, gate, tch,
-                           ncols, nh, xr);
-    } else {
-        auto k = k_dslash_tm<PREC, false, true, G, false, true, LF>;
-        allow_lds(k, lds);
-        hipLaunchKernelGGL(k, grid, bs, lds, s, g, gauge, in, FieldRef{}, kappa, red, gate, tch,
-                           ncols, nh, xr);
-    }
-    launch_finalize(red, g.V / wvol, gate.batch ? gate.mode : -1, s);
+    const March m = march_of<PREC>(g, g.bvol, in.nrhs);
+    if (dagger)
+        launch_tm<PREC, true, true, true, LF>(m, g, gauge, in, FieldRef{}, kappa, red, gate, xr, s);
+    else
+        launch_tm<PREC, false, true, true, LF>(m, g, gauge, in, FieldRef{}, kappa, red, gate, xr, s);
+    launch_finalize(red, tm_partials(g, m.p), gate.batch ? gate.mode : -1, s);
     return true;
 }
 
@@ -891,12 +939,13 @@ __global__ void __launch_bounds__(256) k_hop_half(Geom g, const void *__restrict
 //    U_t (parity 1 - p links), carried in registers.
 // Hops are summed in the order of k_hop_half.  Forward links come from gp at
 // the output entry, backward ones from gq at the neighbour's entry.
-template <int PREC, bool DAG, bool RED, bool HASC, int GROUP, bool XR, int LF>
+// RAG: parts as in k_dslash_tm where a half slice is no whole number of tiles.
+template <int PREC, bool DAG, bool RED, bool HASC, int GROUP, bool XR, int LF, bool RAG>
 __global__ void __launch_bounds__(kTmMaxBlock) k_hop_half_tm(Geom g, const void *__restrict__ gp,
                                                      const void *__restrict__ gq, int p,
                                                      FieldRef in, FieldRef c, FieldRef out,
                                                      double k_d, double cs_d, RedArgs red,
-                                                     Gate gate, int tchunk, int ncols,
+                                                     Gate gate, int tchunk, int ncols, int w,
                                                      XrArgs xr) {
     using R = typename Spinor<PREC>::R;
     extern __shared__ __align__(16) char lds[];
@@ -905,9 +954,8 @@ __global__ void __launch_bounds__(kTmMaxBlock) k_hop_half_tm(Geom g, const void 
     __shared__ double wsum[2][kTmMaxBlock / 64];
     if (gate_off(gate)) return;  // grid-uniform
     const int nrhs = in.nrhs;
-    const int wvol = (int)blockDim.x;  // entries of this workgroup's part
-    const int hvol = g.bvol >> 1;      // entries of one parity per brick slice
-    const int nsub = hvol / wvol;
+    const int hvol = g.bvol >> 1;  // entries of one parity per brick slice
+    const int nsub = RAG ? (hvol + w - 1) / w : hvol / w;
     const int lb = logical_block();
     const int cb = lb / nrhs;
     const int rhs = lb - cb * nrhs;
@@ -918,20 +966,30 @@ __global__ void __launch_bounds__(kTmMaxBlock) k_hop_half_tm(Geom g, const void 
     const int chunk = cc / ncols;
     const int col = cc - chunk * ncols;
     const int Lt = g.L[3];
-    const int l = (int)threadIdx.x;
+    const int tid = (int)threadIdx.x;
+    // entries of this workgroup's part; lanes past it repeat its last
+    const int wvol = RAG && hvol - hp * w < w ? hvol - hp * w : w;
+    const bool mine = !RAG || tid < wvol;
+    const int l = mine ? tid : wvol - 1;
     const int t0 = chunk * tchunk;
     const int t1 = t0 + tchunk < Lt ? t0 + tchunk : Lt;
     // first entry of this workgroup's part of half slice t: hbase + t * hvol
-    const int hbase = col * Lt * hvol + hp * wvol;
+    const int hbase = col * Lt * hvol + hp * w;
     char *img0 = lds;
-    char *img1 = lds + slice_bytes<PREC>(wvol);
+    char *img1 = lds + slice_bytes<PREC>((int)blockDim.x);
     constexpr int SF = DAG ? +1 : -1;
     constexpr int SB = -SF;
     const R kappa = (R)k_d;
 
     // prologue: input half slice t0 into image 0, and the backward t hop of
     // slice t0 from input entry l of slice t0 - 1
-    slice_copy<PREC>(fin, (hbase + t0 * hvol) >> 6, img0);
+    auto copy = [&](int t, char *img) {
+        if constexpr (RAG)
+            slice_copy_ragged<PREC>(fin, hbase + t * hvol + l, img);
+        else
+            slice_copy<PREC>(fin, (hbase + t * hvol) >> 6, img);
+    };
+    copy(t0, img0);
     cx<R> cw0[3], cw1[3];
     {
         const int ip = hbase + (t0 == 0 ? Lt - 1 : t0 - 1) * hvol + l;
@@ -957,7 +1015,7 @@ __global__ void __launch_bounds__(kTmMaxBlock) k_hop_half_tm(Geom g, const void 
         const FieldRef cur = lds_view(fin, odd ? img1 : img0);
         const FieldRef nxt = lds_view(fin, odd ? img0 : img1);
         const int tn = t + 1 < Lt ? t + 1 : 0;
-        slice_copy<PREC>(fin, (hbase + tn * hvol) >> 6, (char *)nxt.data);
+        copy(tn, (char *)nxt.data);
         const int hs = hbase + t * hvol;
         const int H = hs + l;  // output entry
         // (not with 18-real float64 links: registers would spill)
@@ -1022,21 +1080,23 @@ __global__ void __launch_bounds__(kTmMaxBlock) k_hop_half_tm(Geom g, const void 
             if (RED && !XR)
                 nrm += (double)o[k].re * (double)o[k].re + (double)o[k].im * (double)o[k].im;
         }
+        if constexpr (RAG && XR) pin(o);
         if constexpr (XPRE)
-            nrm = xr_site_r<PREC>(xr, rhs, H, (R)gate.st[rhs].alpha, o, rpre);
+            nrm = xr_site_r<PREC>(xr, rhs, H, (R)gate.st[rhs].alpha, o, rpre, mine);
         else if constexpr (XR)
-            nrm = xr_site<PREC>(xr, rhs, H, (R)gate.st[rhs].alpha, o);
+            nrm = xr_site<PREC>(xr, rhs, H, (R)gate.st[rhs].alpha, o, mine);
         else
             Spinor<PREC>::template store<WD_NT_OUT>(rhs_view(out, rhs), H, o);
         if (RED) {
+            if (!mine) nrm = 0.0;
 #pragma unroll
             for (int off = 32; off > 0; off >>= 1) nrm += __shfl_xor(nrm, off, 64);
-            if ((l & 63) == 0) wsum[odd][l >> 6] = nrm;
+            if ((tid & 63) == 0) wsum[odd][tid >> 6] = nrm;
         }
         __syncthreads();  // the current image is free for the next copy
-        if (RED && l == 0) {
+        if (RED && tid == 0) {
             double sum = 0.0;
-            for (int w = 0; w < (wvol >> 6); ++w) sum += wsum[odd][w];
+            for (int v = 0; v < (int)(blockDim.x >> 6); ++v) sum += wsum[odd][v];
             red.partials[(((size_t)col * Lt + t) * nsub + hp) * nrhs + rhs] = sum;
         }
     }
@@ -1052,14 +1112,19 @@ static bool eo_site_forced() {
 // The marching form pays where link and spinor bytes bound the launch: at
 // 48^3 x 96 float64 half launches take 1.29-1.49 ms against 1.65-1.77 one
 // lane per site, float32 -2%, while binary16 (bound by its arithmetic) is
-// 3-8% slower marching and stays one lane per site.
+// 3-8% slower marching and stays one lane per site.  Over half slices that are
+// no whole tiles float64 gains too (30^3 x 60 even-odd CG iteration 1046 ->
+// 1010 us, 22^3 x 44 Schur operator 237 -> 220), float32 does not (30^3 x 60,
+// the two launches of the operator: 114 + 133 us marching, 117 + 127 one lane
+// per site).
 template <int PREC>
-static bool eo_tm_ok(const Geom &g, int nrhs, bool red, int64_t partials_cap) {
-    static const size_t cap = max_lds_per_block();
-    const int w = eo_wvol(g, PREC);
-    return PREC != WD_F16 && w > 0 && !eo_site_forced() && !g_force_site_kernel &&
-           2 * slice_bytes<PREC>(w) + 64 <= cap &&
-           (!red || (int64_t)(g.V / 2 / w) * nrhs <= partials_cap);
+static March eo_march(const Geom &g, int nrhs, bool red, int64_t partials_cap) {
+    March m{};
+    if (PREC == WD_F16 || eo_site_forced()) return m;
+    m = march_of<PREC>(g, g.bvol / 2, nrhs);
+    if (PREC == WD_F32 && m.p.ragged) m.ok = false;
+    if (red && m.ok) m.ok = (int64_t)tm_partials(g, m.p) * nrhs <= partials_cap;
+    return m;
 }
 
 // one half-field launch, marching where the geometry allows, with its
@@ -1070,18 +1135,24 @@ static void launch_eo(const Geom &g, const void *gp, const void *gq, int p, Fiel
                       Gate gate, const XrArgs &xr, hipStream_t s) {
     constexpr int G = HopGroup<PREC>::value;
     int nb;
-    if (eo_tm_ok<PREC>(g, in.nrhs, RED, r.partials_cap)) {
-        const int w = eo_wvol(g, PREC);
-        const int nsub = g.bvol / 2 / w;
-        const int tch = tm_chunk(g, in.nrhs * nsub);
-        const int ncols = g.V / (g.L[3] * g.bvol);
-        const dim3 grid(tm_blocks(g, tch) * nsub * in.nrhs), bs(w);
-        const size_t lds = 2 * slice_bytes<PREC>(w);
-        auto kern = k_hop_half_tm<PREC, DAG, RED, HASC, G, XR, LF>;
-        allow_lds(kern, lds);
-        hipLaunchKernelGGL(kern, grid, bs, lds, s, g, gp, gq, p, in, c, out, k, cs, r, gate, tch,
-                           ncols, xr);
-        nb = g.V / 2 / w;
+    const March m = eo_march<PREC>(g, in.nrhs, RED, r.partials_cap);
+    if (m.ok) {
+        if constexpr (PREC != WD_F16) {
+            auto go = [&](auto kern) {
+                allow_lds(kern, m.lds);
+                hipLaunchKernelGGL(kern, m.grid, m.bs, m.lds, s, g, gp, gq, p, in, c, out, k, cs,
+                                   r, gate, m.tch, m.ncols, m.p.w, xr);
+            };
+            if constexpr (PREC == WD_F64) {
+                if (m.p.ragged)
+                    go(k_hop_half_tm<PREC, DAG, RED, HASC, G, XR, LF, true>);
+                else
+                    go(k_hop_half_tm<PREC, DAG, RED, HASC, G, XR, LF, false>);
+            } else {
+                go(k_hop_half_tm<PREC, DAG, RED, HASC, G, XR, LF, false>);
+            }
+        }
+        nb = tm_partials(g, m.p);
     } else {
         nb = site_blocks(out.V);
         hipLaunchKernelGGL((k_hop_half<PREC, DAG, RED, HASC, G, XR, LF>), dim3(nb * in.nrhs),
@@ -1269,14 +1340,16 @@ void launch_halo_links(const Geom &g, const double *canon, void *links, hipStrea
                        (const double2 *)canon, links);
 }
 
-bool halo_supported(const Geom &g) { return tm_eligible(g) && tm_fits<WD_F64>(g); }
+// (slabs whose bricks are no whole tiles are refused)
+bool halo_supported(const Geom &g) {
+    return tm_eligible(g) && 2 * slice_bytes<WD_F64>(tm_wvol(g, WD_F64)) + 64 <= max_lds_per_block();
+}
 
 template <int LF>
 static void launch_halo_lf(const Geom &g, const void *gauge, double kappa, int dagger,
                            FieldRef in, FieldRef out, const Halo &region, hipStream_t s) {
-    const int wvol = tm_wvol(g, WD_F64);
-    const int nsub = g.bvol / wvol;
-    const int tch = tm_chunk(g, in.nrhs * nsub);
+    const PartShape p = tm_part(g, WD_F64);
+    const int tch = tm_chunk(g, in.nrhs * p.nsub);
     const int ncols = g.V / (g.L[3] * g.bvol);
     // chunks of this launch: all; the interior ones (neither slice 0 nor
     // Lt - 1: no staged face is read); or the one or two holding the ends
@@ -1293,21 +1366,19 @@ static void launch_halo_lf(const Geom &g, const void *gauge, double kappa, int d
         halo.cstep = nch - 1 > 0 ? nch - 1 : 1;
     }
     if (count <= 0) return;
-    const dim3 grid(ncols * count * nsub * in.nrhs), bs(wvol);
-    const size_t lds = 2 * slice_bytes<WD_F64>(wvol);
+    const dim3 grid(ncols * count * p.nsub * in.nrhs), bs(p.threads);
+    const size_t lds = 2 * slice_bytes<WD_F64>(p.threads);
     constexpr int G = HopGroup<WD_F64>::value;
     const Gate none{nullptr, nullptr, GATE_ACTIVE};
-    if (dagger) {
-        auto k = k_dslash_tm<WD_F64, true, false, G, true, false, LF>;
+    auto go = [&](auto k) {
         allow_lds(k, lds);
         hipLaunchKernelGGL(k, grid, bs, lds, s, g, gauge, in, out, kappa, RedArgs{}, none, tch,
-                           ncols, halo, XrArgs{});
-    } else {
-        auto k = k_dslash_tm<WD_F64, false, false, G, true, false, LF>;
-        allow_lds(k, lds);
-        hipLaunchKernelGGL(k, grid, bs, lds, s, g, gauge, in, out, kappa, RedArgs{}, none, tch,
-                           ncols, halo, XrArgs{});
-    }
+                           ncols, p.w, halo, XrArgs{});
+    };
+    if (dagger)
+        go(k_dslash_tm<WD_F64, true, false, G, true, false, LF>);
+    else
+        go(k_dslash_tm<WD_F64, false, false, G, true, false, LF>);
 }
 
 void launch_dslash_halo(const Geom &g, const void *gauge, double kappa, int dagger, FieldRef in,

@@ -399,6 +399,37 @@ inline int eo_wvol(const Geom &g, int prec) {
     return part_sites(hvol, prec);
 }
 
+// How a marching workgroup covers a slice of n sites (entries): parts of w
+// consecutive ones, the last maybe fewer, a workgroup of `threads` lanes each.
+// Slices of whole tiles take the parts above, all full.  Others ("ragged":
+// their parts start anywhere in a tile, and lanes past a part idle) are cut
+// evenly into as few parts as the same limits allow.
+struct PartShape {
+    int w, nsub, threads;
+    bool ragged;
+};
+
+inline PartShape part_shape(int n, int prec) {
+    PartShape p{};
+    if (n % 64 == 0) {
+        p.w = p.threads = part_sites(n, prec);
+        p.nsub = n / p.w;
+        return p;
+    }
+    const int cap = prec == WD_F64 ? 192 : 256;
+    p.nsub = (n + cap - 1) / cap;
+    p.w = (n + p.nsub - 1) / p.nsub;
+    p.threads = (p.w + 63) / 64 * 64;
+    p.ragged = true;
+    return p;
+}
+
+inline PartShape tm_part(const Geom &g, int prec) { return part_shape(g.bvol, prec); }
+inline PartShape eo_part(const Geom &g, int prec) { return part_shape(g.bvol / 2, prec); }
+
+// slices the marching stencils take: whole tiles, or at least half a wave
+inline bool marches(int n) { return n > 0 && (n % 64 == 0 || n >= 32); }
+
 // time slices per chunk: enough workgroups over all rhs to fill the chip (a
 // multiple of 8 chunks where the extent allows); env_chunk > 0 overrides
 // (tuning)
@@ -419,14 +450,21 @@ inline int tm_blocks(const Geom &g, int chunk_len) {
     return ncols * ((g.L[3] + chunk_len - 1) / chunk_len);
 }
 
+// partial sums of a marching launch per rhs: one per part of a slice
+inline int tm_partials(const Geom &g, const PartShape &p) { return g.V / g.bvol * p.nsub; }
+
 // partial sums any reducing launch on this geometry may write (the time
-// marching stencil writes V / w <= V / 64 per rhs)
+// marching stencil over whole tiles writes V / w <= V / 64 per rhs)
 inline int64_t reduce_partials_cap(const Geom &g, int nrhs) {
     int64_t nb = site_blocks(g.V);
-    if (tm_eligible(g)) {
-        const int64_t tmb = (int64_t)g.V / 64;
-        if (tmb > nb) nb = tmb;
-    }
+    auto most = [&](int64_t n) {
+        if (n > nb) nb = n;
+    };
+    if (tm_eligible(g))
+        most((int64_t)g.V / 64);
+    else if (marches(g.bvol))
+        most(tm_partials(g, tm_part(g, WD_F64)));
+    if (marches(g.bvol / 2)) most(tm_partials(g, eo_part(g, WD_F64)));
     return (nb + 1) * nrhs;
 }
 
@@ -440,8 +478,7 @@ inline int64_t reduce_partials_cap(const Geom &g, int nrhs) {
 // of 256; measured 2-4% faster than 384-site bricks), else at most 256; then
 // the fewest neighbours per site outside the float64 workgroup's part of the
 // slice (brick faces, and the boundaries between parts), then the thinner y
-// extent.  Lattices too small for a 64-site brick take whole x rows with the
-// largest y/z divisors up to 8 and 4.
+// extent.  Lattices whose extents give no brick of whole tiles: ragged_bricks.
 // WD_BRICK="tx,ty,tz" overrides the choice (tuning).
 inline int largest_divisor_le(int n, int cap) {
     for (int d = cap < n ? cap : n; d >= 1; --d)
@@ -474,6 +511,34 @@ inline int part_faces(const int L[4], int a, int b, int c, int w) {
     return (int)(out * 240 / (a * b * c));
 }
 
+// Bricks where no extents give whole tiles: whole x rows, and the y and z
+// extents that lose the least to idle lanes and to neighbours outside the
+// parts, over the full slice and the half slice of one parity in float64 (the
+// neighbours counted on the full slice).  A unit of neighbours from outside costs about 7% (48^3 x 96: 2.0 of them 1.86
+// ms, none 1.61), idle lanes their share.
+inline void ragged_bricks(const Geom &g, int &bx, int &by, int &bz) {
+    bx = g.L[0];
+    by = largest_divisor_le(g.L[1], 8);
+    bz = largest_divisor_le(g.L[2], 4);
+    double best = 1e30;
+    for (int b = 1; b <= g.L[1]; ++b) {
+        if (g.L[1] % b) continue;
+        for (int c = 1; c <= g.L[2]; ++c) {
+            const int v = bx * b * c;
+            if (g.L[2] % c || v > 1024 || v < 32) continue;
+            const PartShape p = part_shape(v, WD_F64), q = part_shape(v / 2, WD_F64);
+            double cost = (double)p.nsub * p.threads / v + (double)q.nsub * q.threads / (v / 2);
+            if (cost >= best) continue;
+            cost *= 1.0 + 0.07 * part_faces(g.L, bx, b, c, p.w) / 240.0;
+            if (cost < best - 1e-9) {
+                best = cost;
+                by = b;
+                bz = c;
+            }
+        }
+    }
+}
+
 inline void choose_bricks(Geom &g) {
     int bx = 0, by = 0, bz = 0;
     long long best = 0;
@@ -499,11 +564,7 @@ inline void choose_bricks(Geom &g) {
             }
         }
     }
-    if (!best) {
-        bx = g.L[0];
-        by = largest_divisor_le(g.L[1], 8);
-        bz = largest_divisor_le(g.L[2], 4);
-    }
+    if (!best) ragged_bricks(g, bx, by, bz);
     if (const char *e = getenv("WD_BRICK")) {
         int a = 0, b = 0, c = 0;
         if (sscanf(e, "%d,%d,%d", &a, &b, &c) == 3 && a >= 1 && b >= 1 && c >= 1 &&
