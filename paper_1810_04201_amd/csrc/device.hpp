@@ -305,40 +305,47 @@ struct Link<WD_F16> {
 // |v / s| <= 1, so the sums stay within binary16's range); the site scale s
 // multiplies the hop's float result.
 
-// Two-term dot products of halves accumulated in float32, with the sign
-// modifiers of v_dot2_f32_f16 on the second operand's halves (the compiler
-// does not fold a negated half into the instruction and would spend a
+// Chains of two-term dot products of halves accumulated in float32 from zero,
+// with the sign modifiers of v_dot2_f32_f16 on the second operand's halves (the
+// compiler does not fold a negated half into the instruction and would spend a
 // separate instruction on it):
-//   dot2_pp(a, b, c) = a.x b.x + a.y b.y + c     dot2_pm = a.x b.x - a.y b.y + c
-//   dot2_mp          = -a.x b.x + a.y b.y + c    dot2_mm = -a.x b.x - a.y b.y + c
-// The *0 forms start a chain at c = 0.  A dot product's result may be read
-// by the next dot product of a chain as its accumulator at once, but by any
-// other vector instruction only after three wait states; the compiler does
-// not see inside the asm, so the *_e forms, which end a chain and whose
-// results other instructions read, wait those states themselves.
-#define WD_DOT2(NAME, MODS)                                                                 \
-    __device__ __forceinline__ float NAME(h2_t a, h2_t b, float c) {                        \
-        float d;                                                                            \
-        asm("v_dot2_f32_f16 %0, %1, %2, %3" MODS : "=v"(d) : "v"(a), "v"(b), "v"(c));       \
-        return d;                                                                           \
-    }                                                                                       \
-    __device__ __forceinline__ float NAME##0(h2_t a, h2_t b) {                              \
-        float d;                                                                            \
-        asm("v_dot2_f32_f16 %0, %1, %2, 0" MODS : "=v"(d) : "v"(a), "v"(b));                \
-        return d;                                                                           \
-    }                                                                                       \
-    __device__ __forceinline__ float NAME##_e(h2_t a, h2_t b, float c) {                    \
-        float d;                                                                            \
-        asm("v_dot2_f32_f16 %0, %1, %2, %3" MODS "\n\ts_nop 2"                              \
-            : "=v"(d)                                                                       \
-            : "v"(a), "v"(b), "v"(c));                                                      \
-        return d;                                                                           \
-    }
-WD_DOT2(dot2_pp, "")
-WD_DOT2(dot2_pm, " neg_hi:[0,1,0]")
-WD_DOT2(dot2_mp, " neg_lo:[0,1,0]")
-WD_DOT2(dot2_mm, " neg_lo:[0,1,0] neg_hi:[0,1,0]")
-#undef WD_DOT2
+//   dot2_pm3(a, b, c, d, e, f) = a.x b.x - a.y b.y + c.x d.x - c.y d.y + e.x f.x - e.y f.y
+//   dot2_mp_pm(a, b, c, d)     = -a.x b.x + a.y b.y + c.x d.x - c.y d.y
+//   dot2_mm_pp(a, b, c, d)     = -a.x b.x - a.y b.y + c.x d.x + c.y d.y
+// A dot product's register may be the accumulator of the next one at once, but
+// any other vector instruction may read or overwrite it only after three wait
+// states, and the compiler does not see inside the asm.  So a chain is one block
+// on one register that ends with those states: with a block per product the
+// compiler may give a link's register, dead once the next has read it, to
+// another instruction one state later.
+__device__ __forceinline__ float dot2_pm3(h2_t a, h2_t b, h2_t c, h2_t d, h2_t e, h2_t f) {
+    float r;
+    asm("v_dot2_f32_f16 %0, %1, %2, 0 neg_hi:[0,1,0]\n\t"
+        "v_dot2_f32_f16 %0, %3, %4, %0 neg_hi:[0,1,0]\n\t"
+        "v_dot2_f32_f16 %0, %5, %6, %0 neg_hi:[0,1,0]\n\t"
+        "s_nop 2"
+        : "=&v"(r)
+        : "v"(a), "v"(b), "v"(c), "v"(d), "v"(e), "v"(f));
+    return r;
+}
+__device__ __forceinline__ float dot2_mp_pm(h2_t a, h2_t b, h2_t c, h2_t d) {
+    float r;
+    asm("v_dot2_f32_f16 %0, %1, %2, 0 neg_lo:[0,1,0]\n\t"
+        "v_dot2_f32_f16 %0, %3, %4, %0 neg_hi:[0,1,0]\n\t"
+        "s_nop 2"
+        : "=&v"(r)
+        : "v"(a), "v"(b), "v"(c), "v"(d));
+    return r;
+}
+__device__ __forceinline__ float dot2_mm_pp(h2_t a, h2_t b, h2_t c, h2_t d) {
+    float r;
+    asm("v_dot2_f32_f16 %0, %1, %2, 0 neg_lo:[0,1,0] neg_hi:[0,1,0]\n\t"
+        "v_dot2_f32_f16 %0, %3, %4, %0\n\t"
+        "s_nop 2"
+        : "=&v"(r)
+        : "v"(a), "v"(b), "v"(c), "v"(d));
+    return r;
+}
 
 __device__ __forceinline__ h2_t h2_swap(h2_t b) { return __builtin_shufflevector(b, b, 1, 0); }
 
@@ -358,8 +365,8 @@ __device__ __forceinline__ void Link<WD_F16>::load_h2(const void *g, int mu, int
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
         const int j1 = (j + 1) % 3, j2 = (j + 2) % 3;
-        const float re = dot2_pm_e(u[j1], u[3 + j2], dot2_mp0(u[j2], u[3 + j1]));
-        const float im = dot2_pp_e(u[j1], s1[j2], dot2_mm0(u[j2], s1[j1]));
+        const float re = dot2_mp_pm(u[j2], u[3 + j1], u[j1], u[3 + j2]);
+        const float im = dot2_mm_pp(u[j2], s1[j1], u[j1], s1[j2]);
         u[6 + j] = h2_t{(_Float16)re, (_Float16)(-im)};
     }
 }
@@ -410,9 +417,9 @@ __device__ __forceinline__ void su3_mul_h2(const h2_t u[9], const h2_t h[3], cx<
         };
         if (ADJ) {
             re = pp3(m0, h[0], m1, h[1], m2, h[2]);
-            im = dot2_pm_e(m2, hs[2], dot2_pm(m1, hs[1], dot2_pm0(m0, hs[0])));
+            im = dot2_pm3(m0, hs[0], m1, hs[1], m2, hs[2]);
         } else {
-            re = dot2_pm_e(m2, h[2], dot2_pm(m1, h[1], dot2_pm0(m0, h[0])));
+            re = dot2_pm3(m0, h[0], m1, h[1], m2, h[2]);
             im = pp3(m0, hs[0], m1, hs[1], m2, hs[2]);
         }
         w[a] = {re, im};
