@@ -13,23 +13,28 @@ static constexpr int kBS = 256;  // gauge kernels (one lane per site)
 
 // ------------------------------------------------------------------ reduction phase 2
 
-// One block: fixed-order sum of nb partials per rhs, then the finaliser.
-// The order for an rhs does not depend on nrhs (thread t sums partials
-// t + 4jT, t + (4j+1)T, t + (4j+2)T, t + (4j+3)T into four running sums,
-// T = 1024; a butterfly inside each wave; the 16 waves in order), so a
-// batched solve reproduces the single-rhs solves bit for bit.
-// gate_mode >= 0: skipped when the producing kernel's batch gate was off
-// (it returned early and wrote no partials).
+// Fixed-order sum of the nb partials of an rhs, then the finaliser.  The order
+// does not depend on nrhs (thread t sums partials t + 4jT, t + (4j+1)T,
+// t + (4j+2)T, t + (4j+3)T into four running sums, T = 1024; a butterfly inside
+// each wave; the 16 waves in order), so a batched solve reproduces the
+// single-rhs solves bit for bit.  A block per rhs: 12 of them over 3456
+// partials each took one block 24 us.  RED_TRUE tests the states of all rhs
+// (a reliable update whose gate was off wrote no partials), so one block does
+// them all.
 constexpr int kFinalizeThreads = 1024;
 
-__global__ void __launch_bounds__(kFinalizeThreads) k_finalize(RedArgs red, int nb, int gate_mode) {
-    if (gate_mode >= 0 && gate_off(Gate{nullptr, red.batch, gate_mode})) return;
+__global__ void __launch_bounds__(kFinalizeThreads) k_finalize(RedArgs red, int nb) {
+    if (red.mode == RED_TRUE) {
+        const bool off = gate_off(Gate{red.st, red.ctl.nrhs, GATE_TRIGGER});
+        __syncthreads();  // the states are read before any is written
+        if (off) return;
+    }
     constexpr int T = kFinalizeThreads, NW = T / 64;
     __shared__ double sm[NW * 12];
     const int nrhs = red.ctl.nrhs;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const double *P = red.partials;
-    for (int r = 0; r < nrhs; ++r) {
+    for (int r = blockIdx.x; r < nrhs; r += gridDim.x) {
         double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
         int b = tid;
         for (; b + 3 * T < nb; b += 4 * T) {
@@ -45,17 +50,17 @@ __global__ void __launch_bounds__(kFinalizeThreads) k_finalize(RedArgs red, int 
         if (lane == 0) sm[w * 12 + r] = v;
     }
     __syncthreads();
-    if (tid < nrhs && red.mode != RED_NONE) {
+    for (int r = blockIdx.x + tid * gridDim.x; r < nrhs; r += kFinalizeThreads * gridDim.x) {
         double t = 0.0;
-        for (int k = 0; k < NW; ++k) t += sm[k * 12 + tid];
-        finalize_rhs(red, tid, t);
+        for (int k = 0; k < NW; ++k) t += sm[k * 12 + r];
+        if (red.mode != RED_NONE) finalize_state(red.st[r], red.ctl, red.mode, t);
     }
-    __syncthreads();
-    if (tid == 0 && red.mode != RED_NONE) recount_batch(red);
 }
 
-void launch_finalize(const RedArgs &red, int nb, int gate_mode, hipStream_t s) {
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kFinalizeThreads), 0, s, red, nb, gate_mode);
+void launch_finalize(const RedArgs &red, int nb, hipStream_t s) {
+    if (red.deferred) return;
+    hipLaunchKernelGGL(k_finalize, dim3(red.mode == RED_TRUE ? 1 : red.ctl.nrhs),
+                       dim3(kFinalizeThreads), 0, s, red, nb);
 }
 
 // ------------------------------------------------------------------ gauge
@@ -268,18 +273,6 @@ __global__ void k_export_half(FieldRef f, double2 *__restrict__ canon, int p, Ge
     for (int k = 0; k < 12; ++k) dst[k] = make_double2(v[k].re, v[k].im);
 }
 
-template <int SRC, int DST>
-__global__ void k_convert(FieldRef a, FieldRef b, Gate gate) {
-    if (gate_off(gate)) return;
-    const int r = blockIdx.y;
-    if (!gate_rhs(gate, r)) return;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= a.V) return;
-    cx<double> v[12];
-    load_as_double<SRC>(rhs_view(a, r), i, v);
-    store_from_double<DST>(rhs_view(b, r), i, v);
-}
-
 template <int PREC>
 __global__ void k_zero(FieldRef f) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -354,20 +347,6 @@ void launch_export_half(FieldRef f, double *canon, int p, const Geom &geo, hipSt
                                                 0, s, f, (double2 *)canon, p, geo));
 }
 
-template <int SRC>
-static void convert_to(FieldRef a, FieldRef b, Gate gate, hipStream_t s) {
-    const dim3 gr = field_grid(a), bs(kSiteBlock);
-    switch (b.prec) {
-        case WD_F64: hipLaunchKernelGGL((k_convert<SRC, WD_F64>), gr, bs, 0, s, a, b, gate); break;
-        case WD_F32: hipLaunchKernelGGL((k_convert<SRC, WD_F32>), gr, bs, 0, s, a, b, gate); break;
-        default: hipLaunchKernelGGL((k_convert<SRC, WD_F16>), gr, bs, 0, s, a, b, gate); break;
-    }
-}
-
-void launch_convert(FieldRef a, FieldRef b, Gate gate, hipStream_t s) {
-    WD_DISPATCH_PREC(a.prec, convert_to<PP>(a, b, gate, s));
-}
-
 void launch_zero(FieldRef f, hipStream_t s) {
     WD_DISPATCH_PREC(f.prec,
                      hipLaunchKernelGGL(k_zero<PP>, field_grid(f), dim3(kSiteBlock), 0, s, f));
@@ -418,33 +397,60 @@ __global__ void __launch_bounds__(kSiteBlock) k_update_xr(FieldRef x, FieldRef r
     reduce_block(nrm, red.partials, (size_t)blockIdx.x * x.nrhs + rhs);
 }
 
-// p = r + beta p (RESTART: at the first reliable update p = r)
-template <int PX, int PPP, bool RESTART>
+// p = r + beta p
+template <int PX, int PPP>
 __global__ void k_update_p(FieldRef p, FieldRef r, Gate gate) {
-    if (gate_off(gate)) return;
+    const int rhs = blockIdx.y;
+    if (!gate_rhs(gate, rhs)) return;
+    using R = typename Spinor<PX>::R;
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    using RP = typename Spinor<PPP>::R;
+    if (i >= p.V) return;
+    const FieldRef pf = rhs_view(p, rhs);
+    const R beta = (R)gate.st[rhs].beta;
+    cx<R> rv[12];
+    cx<RP> q[12];
+    Spinor<PX>::load(rhs_view(r, rhs), i, rv);
+    Spinor<PPP>::load(pf, i, q);
+#pragma unroll
+    for (int k = 0; k < 12; ++k)
+        q[k] = {(RP)(rv[k].re + beta * (R)q[k].re), (RP)(rv[k].im + beta * (R)q[k].im)};
+    Spinor<PPP>::store(pf, i, q);
+}
+
+// After a reliable update: r_lo = r64 rounded to its format, p = r_lo + beta p
+// (at the first update p = r_lo), with r_lo as stored.
+template <int PX, int PPP>
+__global__ void k_restart(FieldRef r64, FieldRef rlo, FieldRef p, Gate gate) {
     const int rhs = blockIdx.y;
     if (!gate_rhs(gate, rhs)) return;
     const RhsState &st = gate.st[rhs];
     using R = typename Spinor<PX>::R;
+    using RP = typename Spinor<PPP>::R;
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= p.V) return;
-    const FieldRef pf = rhs_view(p, rhs);
-    cx<R> rv[12], pv[12];
-    Spinor<PX>::load(rhs_view(r, rhs), i, rv);
-    if (RESTART && st.updates == 1) {
+    const FieldRef pf = rhs_view(p, rhs), rf = rhs_view(rlo, rhs);
+    cx<double> d[12];
+    Spinor<WD_F64>::load(rhs_view(r64, rhs), i, d);
+    store_from_double<PX>(rf, i, d);
+    cx<R> rv[12];
+    if constexpr (PX == WD_F16) {
+        Spinor<PX>::load(rf, i, rv);
+    } else {
 #pragma unroll
-        for (int k = 0; k < 12; ++k) pv[k] = rv[k];
+        for (int k = 0; k < 12; ++k) rv[k] = {(R)d[k].re, (R)d[k].im};
+    }
+    cx<RP> o[12];
+    if (st.updates == 1) {
+#pragma unroll
+        for (int k = 0; k < 12; ++k) o[k] = {(RP)rv[k].re, (RP)rv[k].im};
     } else {
         const R beta = (R)st.beta;
-        cx<typename Spinor<PPP>::R> q[12];
-        Spinor<PPP>::load(pf, i, q);
+        Spinor<PPP>::load(pf, i, o);
 #pragma unroll
         for (int k = 0; k < 12; ++k)
-            pv[k] = {rv[k].re + beta * (R)q[k].re, rv[k].im + beta * (R)q[k].im};
+            o[k] = {(RP)(rv[k].re + beta * (R)o[k].re), (RP)(rv[k].im + beta * (R)o[k].im)};
     }
-    cx<typename Spinor<PPP>::R> o[12];
-#pragma unroll
-    for (int k = 0; k < 12; ++k) o[k] = {(typename Spinor<PPP>::R)pv[k].re, (typename Spinor<PPP>::R)pv[k].im};
     Spinor<PPP>::store(pf, i, o);
 }
 
@@ -457,27 +463,60 @@ __global__ void k_update_p(FieldRef p, FieldRef r, Gate gate) {
 // x += alpha p ; p = r + beta p: the x update of the iteration whose r
 // update a stencil did, merged with the p update (p read once).  Same
 // arithmetic as k_update_xr's x update and k_update_p.
-template <int PX, int PPP>
-__global__ void k_update_xp(FieldRef x, FieldRef p, FieldRef r, Gate gate) {
-    if (gate_off(gate)) return;
+// DEFER: the reduction of |r|^2 that gives beta is finished here (Cons); the
+// fields are loaded before it is waited for.
+template <int PX, int PPP, bool DEFER>
+__global__ void __launch_bounds__(kSiteBlock) k_update_xp(FieldRef x, FieldRef p, FieldRef r,
+                                                          Gate gate, Cons rr, SolveCtl ctl) {
     const int rhs = blockIdx.y;
-    if (!gate_rhs(gate, rhs)) return;
-    const RhsState &st = gate.st[rhs];
     using R = typename Spinor<PX>::R;
     using RP = typename Spinor<PPP>::R;
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= p.V) return;
-    const FieldRef xf = rhs_view(x, rhs), pf = rhs_view(p, rhs);
-    const R alpha = (R)st.alpha, beta = (R)st.beta;
+    const FieldRef xf = rhs_view(x, rhs), pf = rhs_view(p, rhs), rf = rhs_view(r, rhs);
+    Deferred d{};
+    if constexpr (DEFER) d = defer_load(rr, ctl.nrhs, rhs);
+    if constexpr (DEFER) {
+        const RhsState &f = rr.from[rhs];  // not written by this kernel
+        if (!f.active) {
+            // failed at the first reduction: the iterate's state learns it here
+            if (f.failed && blockIdx.x == 0 && threadIdx.x == 0) copy_state(rr.next[rhs], f);
+            return;
+        }
+    } else {
+        if (!gate_rhs(gate, rhs)) return;
+    }
     cx<RP> q[12];
-    cx<R> v[12];
-    Spinor<PPP>::template load<WD_NT_XP>(pf, i, q);
-    Spinor<PX>::template load<WD_NT_XP>(xf, i, v);
+    cx<R> v[12], w[DEFER ? 12 : 1];
+    R alpha, beta;
+    if constexpr (DEFER) {
+        if (i < p.V) {
+            Spinor<PPP>::template load<WD_NT_XP>(pf, i, q);
+            Spinor<PX>::template load<WD_NT_XP>(xf, i, v);
+            Spinor<PX>::template load<WD_NT_XP>(rf, i, w);
+        }
+        const RhsState &s = rr.from[rhs];
+        const double total = uniform(defer_sum(rr, d));
+        if (blockIdx.x == 0) defer_write(rr, ctl, RED_RR, rhs, total);
+        if (!rr_goes_on(s, ctl, total) || i >= p.V) return;
+        alpha = (R)s.alpha;
+        beta = (R)(total / s.rr);
+    } else {
+        if (i >= p.V) return;
+        alpha = (R)gate.st[rhs].alpha;
+        beta = (R)gate.st[rhs].beta;
+        Spinor<PPP>::template load<WD_NT_XP>(pf, i, q);
+        Spinor<PX>::template load<WD_NT_XP>(xf, i, v);
+    }
 #pragma unroll
     for (int k = 0; k < 12; ++k)
         v[k] = {v[k].re + alpha * (R)q[k].re, v[k].im + alpha * (R)q[k].im};
     Spinor<PX>::template store<WD_NT_XP>(xf, i, v);
-    Spinor<PX>::template load<WD_NT_XP>(rhs_view(r, rhs), i, v);
+    if constexpr (DEFER) {
+#pragma unroll
+        for (int k = 0; k < 12; ++k) v[k] = w[k];
+    } else {
+        Spinor<PX>::template load<WD_NT_XP>(rf, i, v);
+    }
     cx<RP> o[12];
 #pragma unroll
     for (int k = 0; k < 12; ++k)
@@ -485,14 +524,24 @@ __global__ void k_update_xp(FieldRef x, FieldRef p, FieldRef r, Gate gate) {
     Spinor<PPP>::template store<WD_NT_XP>(pf, i, o);
 }
 
-void launch_update_xp(FieldRef x, FieldRef p, FieldRef r, Gate gate, hipStream_t s) {
+template <bool DEFER>
+static void update_xp_impl(FieldRef x, FieldRef p, FieldRef r, Gate gate, const Cons &rr,
+                           const SolveCtl &ctl, hipStream_t s) {
     const dim3 gr = field_grid(p), bs(kSiteBlock);
     if (x.prec == WD_F64)
-        hipLaunchKernelGGL((k_update_xp<WD_F64, WD_F64>), gr, bs, 0, s, x, p, r, gate);
+        hipLaunchKernelGGL((k_update_xp<WD_F64, WD_F64, DEFER>), gr, bs, 0, s, x, p, r, gate, rr, ctl);
     else if (p.prec == WD_F32)
-        hipLaunchKernelGGL((k_update_xp<WD_F32, WD_F32>), gr, bs, 0, s, x, p, r, gate);
+        hipLaunchKernelGGL((k_update_xp<WD_F32, WD_F32, DEFER>), gr, bs, 0, s, x, p, r, gate, rr, ctl);
     else
-        hipLaunchKernelGGL((k_update_xp<kF16XrPrec, WD_F16>), gr, bs, 0, s, x, p, r, gate);
+        hipLaunchKernelGGL((k_update_xp<kF16XrPrec, WD_F16, DEFER>), gr, bs, 0, s, x, p, r, gate, rr, ctl);
+}
+
+void launch_update_xp(FieldRef x, FieldRef p, FieldRef r, Gate gate, const Cons &rr,
+                      const SolveCtl &ctl, hipStream_t s) {
+    if (rr.nb)
+        update_xp_impl<true>(x, p, r, gate, rr, ctl, s);
+    else
+        update_xp_impl<false>(x, p, r, gate, rr, ctl, s);
 }
 
 void launch_update_xr(FieldRef x, FieldRef r, FieldRef p, FieldRef Ap, const RedArgs &red,
@@ -504,26 +553,27 @@ void launch_update_xr(FieldRef x, FieldRef r, FieldRef p, FieldRef Ap, const Red
         hipLaunchKernelGGL((k_update_xr<WD_F32, WD_F32>), gr, bs, 0, s, x, r, p, Ap, red, gate);
     else
         hipLaunchKernelGGL((k_update_xr<kF16XrPrec, WD_F16>), gr, bs, 0, s, x, r, p, Ap, red, gate);
-    launch_finalize(red, gr.x, GATE_ACTIVE, s);
-}
-
-template <bool RESTART>
-static void update_p_impl(FieldRef p, FieldRef r, Gate gate, hipStream_t s) {
-    const dim3 gr = field_grid(p), bs(kSiteBlock);
-    if (r.prec == WD_F64)
-        hipLaunchKernelGGL((k_update_p<WD_F64, WD_F64, RESTART>), gr, bs, 0, s, p, r, gate);
-    else if (p.prec == WD_F32)
-        hipLaunchKernelGGL((k_update_p<WD_F32, WD_F32, RESTART>), gr, bs, 0, s, p, r, gate);
-    else
-        hipLaunchKernelGGL((k_update_p<kF16XrPrec, WD_F16, RESTART>), gr, bs, 0, s, p, r, gate);
+    launch_finalize(red, gr.x, s);
 }
 
 void launch_update_p(FieldRef p, FieldRef r, Gate gate, hipStream_t s) {
-    update_p_impl<false>(p, r, gate, s);
+    const dim3 gr = field_grid(p), bs(kSiteBlock);
+    if (r.prec == WD_F64)
+        hipLaunchKernelGGL((k_update_p<WD_F64, WD_F64>), gr, bs, 0, s, p, r, gate);
+    else if (p.prec == WD_F32)
+        hipLaunchKernelGGL((k_update_p<WD_F32, WD_F32>), gr, bs, 0, s, p, r, gate);
+    else
+        hipLaunchKernelGGL((k_update_p<kF16XrPrec, WD_F16>), gr, bs, 0, s, p, r, gate);
 }
 
-void launch_restart_p(FieldRef p, FieldRef r, Gate gate, hipStream_t s) {
-    update_p_impl<true>(p, r, gate, s);
+void launch_restart(FieldRef r64, FieldRef rlo, FieldRef p, Gate gate, hipStream_t s) {
+    const dim3 gr = field_grid(p), bs(kSiteBlock);
+    if (rlo.prec == WD_F64)
+        hipLaunchKernelGGL((k_restart<WD_F64, WD_F64>), gr, bs, 0, s, r64, rlo, p, gate);
+    else if (p.prec == WD_F32)
+        hipLaunchKernelGGL((k_restart<WD_F32, WD_F32>), gr, bs, 0, s, r64, rlo, p, gate);
+    else
+        hipLaunchKernelGGL((k_restart<kF16XrPrec, WD_F16>), gr, bs, 0, s, r64, rlo, p, gate);
 }
 
 // ------------------------------------------------------------------ residual / norms
@@ -570,31 +620,21 @@ void launch_residual(FieldRef r, FieldRef b, FieldRef Ax, const RedArgs &red, Ga
                      hipStream_t s) {
     const dim3 gr = field_grid(r);
     hipLaunchKernelGGL(k_residual, gr, dim3(kSiteBlock), 0, s, r, b, Ax, red, gate);
-    launch_finalize(red, gr.x, gate.batch ? gate.mode : -1, s);
+    launch_finalize(red, gr.x, s);
 }
 
 void launch_norm(FieldRef f, const RedArgs &red, hipStream_t s) {
     const dim3 gr = field_grid(f);
     WD_DISPATCH_PREC(f.prec, hipLaunchKernelGGL(k_norm<PP>, gr, dim3(kSiteBlock), 0, s, f, red));
-    launch_finalize(red, gr.x, -1, s);
+    launch_finalize(red, gr.x, s);
 }
 
-__global__ void k_init_state(RhsState *st, BatchState *batch, int nrhs) {
-    const int r = threadIdx.x;
-    if (r < nrhs) {
-        RhsState z{};
-        st[r] = z;
-    }
-    if (r == 0) {
-        batch->n_active = 0;
-        batch->n_trigger = 0;
-        batch->n_done = 0;
-        batch->pad = 0;
-    }
+__global__ void k_init_state(RhsState *st, RhsState *st2, int nrhs) {
+    if ((int)threadIdx.x < nrhs) st[threadIdx.x] = st2[threadIdx.x] = RhsState{};
 }
 
-void launch_init_state(RhsState *st, BatchState *batch, int nrhs, hipStream_t s) {
-    hipLaunchKernelGGL(k_init_state, dim3(1), dim3(64), 0, s, st, batch, nrhs);
+void launch_init_state(RhsState *st, RhsState *st2, int nrhs, hipStream_t s) {
+    hipLaunchKernelGGL(k_init_state, dim3(1), dim3(64), 0, s, st, st2, nrhs);
 }
 
 }  // namespace wd

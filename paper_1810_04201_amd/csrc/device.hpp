@@ -659,9 +659,13 @@ __device__ __forceinline__ bool finite(double x) { return __builtin_isfinite(x);
 
 // the launch is off for this gate (uniform over the grid)
 __device__ __forceinline__ bool gate_off(const Gate &g) {
-    if (!g.batch) return false;
-    if (g.mode == GATE_TRIGGER) return !(g.batch->n_active == 0 && g.batch->n_trigger > 0);
-    return g.batch->n_active == 0;
+    if (!g.st || g.mode != GATE_TRIGGER) return false;
+    int active = 0, waiting = 0;
+    for (int r = 0; r < g.nrhs; ++r) {
+        active |= g.st[r].active;
+        waiting |= g.st[r].trigger;
+    }
+    return active || !waiting;
 }
 
 // the gate takes right-hand side r (uniform over a workgroup)
@@ -673,10 +677,9 @@ __device__ __forceinline__ bool gate_rhs(const Gate &g, int r) {
     return s.active != 0;
 }
 
-__device__ inline void finalize_rhs(const RedArgs &red, int r, double total) {
-    RhsState &st = red.st[r];
-    const SolveCtl &c = red.ctl;
-    switch (red.mode) {
+__device__ __forceinline__ void finalize_state(RhsState &st, const SolveCtl &c, int mode,
+                                               double total) {
+    switch (mode) {
         case RED_ALPHA:
             st.restarted = 0;
             if (st.active) {
@@ -766,19 +769,6 @@ __device__ inline void finalize_rhs(const RedArgs &red, int r, double total) {
     }
 }
 
-__device__ inline void recount_batch(const RedArgs &red) {
-    int na = 0, nt = 0, nd = 0;
-    for (int r = 0; r < red.ctl.nrhs; ++r) {
-        const RhsState &st = red.st[r];
-        na += st.active;
-        nt += st.trigger;
-        nd += (st.converged || (st.failed && !st.trigger)) ? 1 : 0;
-    }
-    red.batch->n_active = na;
-    red.batch->n_trigger = nt;
-    red.batch->n_done = nd;
-}
-
 // Phase 1.  v: this thread's contribution (0 for idle threads).  Must be
 // reached by every thread of the block; blockDim.x is a multiple of 64.  A
 // fixed butterfly inside each wave, then wave sums in order; writes
@@ -797,6 +787,106 @@ __device__ inline void reduce_block(double v, double *partials, size_t idx) {
     }
 }
 
-// Phase 2 is k_finalize (blas.hip), launched by launch_finalize.
+// Phase 2 is k_finalize (blas.hip), launched by launch_finalize, or on small
+// lattices the kernel that needs the sum (Cons): its workgroups all sum the same
+// few partials, so that an iteration is three launches instead of five.  The
+// loads are issued first (defer_load) and used after the kernel's own first
+// loads are on their way (defer_step): waited for at once they cost the two
+// kernels of a 16^3 x 32 iteration 15 us, more than the two launches of
+// k_finalize (9.3 us and the gaps).
+
+// a thread's share of the nb <= kDeferLoads * blockDim.x partials (the loads are
+// unconditional: part holds at least one)
+struct Deferred {
+    double a[kDeferLoads];
+};
+
+__device__ __forceinline__ Deferred defer_load(const Cons &c, int nrhs, int r) {
+    Deferred d;
+    const int n = blockDim.x;
+#pragma unroll
+    for (int k = 0; k < kDeferLoads; ++k) {
+        const int i = (int)threadIdx.x + k * n;
+        d.a[k] = c.part[(size_t)(i < c.nb ? i : 0) * nrhs + r];
+    }
+    return d;
+}
+
+// the sum, to all threads; reached by all threads of a block of whole waves, a
+// barrier inside
+__device__ __forceinline__ double defer_sum(const Cons &c, const Deferred &d) {
+    __shared__ double sm[16];
+    double v = 0.0;
+#pragma unroll
+    for (int k = 0; k < kDeferLoads; ++k)
+        v += (int)threadIdx.x + k * (int)blockDim.x < c.nb ? d.a[k] : 0.0;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
+    __syncthreads();
+    double total = sm[0];
+    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) total += sm[w];
+    return total;
+}
+
+// the workgroup that hands the state on (one per rhs) steps it; member by
+// member, as a copy of the whole record goes through scratch memory
+__device__ __forceinline__ void copy_state(RhsState &d, const RhsState &s) {
+    d.rr = s.rr;
+    d.rr0 = s.rr0;
+    d.rr_prev = s.rr_prev;
+    d.rr_max = s.rr_max;
+    d.alpha = s.alpha;
+    d.beta = s.beta;
+    d.tt = s.tt;
+    d.rr_true = s.rr_true;
+    d.aux = s.aux;
+    d.aux2 = s.aux2;
+    d.active = s.active;
+    d.converged = s.converged;
+    d.trigger = s.trigger;
+    d.failed = s.failed;
+    d.iters = s.iters;
+    d.since = s.since;
+    d.updates = s.updates;
+    d.restarted = s.restarted;
+    d.pend = s.pend;
+}
+__device__ __forceinline__ void defer_write(const Cons &c, const SolveCtl &ctl, int mode, int r,
+                                            double total) {
+    if (threadIdx.x != 0) return;
+    RhsState s;
+    copy_state(s, c.from[r]);
+    finalize_state(s, ctl, mode, total);
+    copy_state(c.next[r], s);
+}
+
+// an rhs that the iteration skips: so says the state handed on (to be called by
+// the workgroup that hands it on).  The kernel that finishes the second reduction
+// gates on that state alone; the iterate's own it steps itself, and the waves of a
+// workgroup that starts late could read it before and after.
+__device__ __forceinline__ void defer_skip(const Cons &c, int r) {
+    if (c.nb && threadIdx.x == 0) c.next[r].active = 0;
+}
+
+// whether the rhs goes on after RED_ALPHA / RED_RR found `total`: what
+// finalize_state leaves in active
+__device__ __forceinline__ bool alpha_goes_on(double total) {
+    return total > 0.0 && finite(total);
+}
+__device__ __forceinline__ bool rr_goes_on(const RhsState &s, const SolveCtl &c, double total) {
+    if (!s.active || !finite(total)) return false;
+    const double most = total > s.rr_max ? total : s.rr_max;
+    return !(total <= c.tol2 * s.rr0 || (c.mixed && total < c.delta2 * most) ||
+             (c.max_inner > 0 && s.since + 1 >= c.max_inner) || s.iters + 1 >= c.max_iter);
+}
+
+// a double that is the same in all lanes, in scalar registers
+__device__ __forceinline__ double uniform(double x) {
+    const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)b);
+    const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(b >> 32));
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
 
 }  // namespace wd

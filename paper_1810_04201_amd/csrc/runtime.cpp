@@ -265,7 +265,7 @@ void apply_fields(wd_lattice *lat, const void *gauge, double kappa, int dagger,
         });
         return;
     }
-    dslash(lat, gauge, kappa, dagger, a, b, nullptr, Gate{nullptr, nullptr, GATE_ACTIVE}, s);
+    dslash(lat, gauge, kappa, dagger, a, b, nullptr, Gate{nullptr, 0, GATE_ACTIVE}, s);
     launch_export(b, out, lat->g, s);
 }
 
@@ -515,7 +515,7 @@ int wd_dslash(wd_lattice *lat, double kappa, int dagger, const wd_field *in, wd_
     hipStream_t s = (hipStream_t)stream;
     void *g = gauge_for(lat, in->prec, s, &err);
     if (!g) return err;
-    dslash(lat, g, kappa, dagger, in->ref, out->ref, nullptr, Gate{nullptr, nullptr, GATE_ACTIVE}, s);
+    dslash(lat, g, kappa, dagger, in->ref, out->ref, nullptr, Gate{nullptr, 0, GATE_ACTIVE}, s);
     WD_LAUNCH_CHECK();
     return WD_OK;
 }
@@ -591,7 +591,7 @@ int wd_apply_schur(wd_lattice *lat, double kappa, int prec, int dagger, int nrhs
     FieldRef to = carve(cur, prec, nrhs, Vh);
     cur = (char *)mem + 2 * one;
     FieldRef oe = carve(cur, prec, nrhs, Vh);
-    const Gate none{nullptr, nullptr, GATE_ACTIVE};
+    const Gate none{nullptr, 0, GATE_ACTIVE};
     launch_import_half(in, ve, 0, lat->g, s);
     // t_o = D_oe v_e ; out_e = v_e - D_eo t_o  (D^dag's blocks for dagger)
     hop_half(lat, gh, 1, kappa, 0.0, dagger, ve, FieldRef{}, to, nullptr, none, s);

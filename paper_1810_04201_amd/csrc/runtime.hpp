@@ -129,7 +129,6 @@ FieldRef carve(char *&cursor, int prec, int nrhs, int V);
 struct SlotRes {
     static constexpr int kSlots = 6;
     RhsState *h_st = nullptr;       // kSlots * 12 (one ring slot per status read)
-    BatchState *h_batch = nullptr;  // kSlots
     hipEvent_t ev[kSlots] = {};
     hipEvent_t final_ev = nullptr;
     int create();
@@ -168,11 +167,11 @@ class Solve {
     void enqueue_reliable();
     void op(bool first, const FieldRef &in, const FieldRef &out, const RedArgs *red, Gate gate,
             bool lo);
-    bool op_xr(const FieldRef &in, const RedArgs &rr, Gate gate);
+    bool op_xr(const FieldRef &in, const XrArgs &xr, const RedArgs &rr, Gate gate);
     void enqueue_finish();
     int push_status();
     RedArgs red(int mode) const;
-    Gate gate() const { return Gate{st_, batch_, GATE_ACTIVE}; }
+    Gate gate() const { return Gate{st_, p_.nrhs, GATE_ACTIVE}; }
 
     wd_lattice *lat_;
     wd_solve_params p_;
@@ -196,7 +195,11 @@ class Solve {
     FieldRef xl_{}, rl_{}, pl_{}, tl_{}, apl_{};
     FieldRef bo64_{}, tmp64_{}, tmpl_{};  // even-odd: b_o and odd temporaries
     RhsState *st_ = nullptr;
-    BatchState *batch_ = nullptr;
+    // the state between the two reductions of an iteration, and the second
+    // one's partials, where the kernels finish them (Cons)
+    RhsState *st2_ = nullptr;
+    double *partials2_ = nullptr;
+    int defer_ = 0;  // partials of such a reduction (0: k_finalize does them)
     double *partials_ = nullptr;
     int partials_cap_ = 0;
     SolveCtl ctl_{};
@@ -205,7 +208,6 @@ class Solve {
     SlotRes own_{};
     SlotRes *res_ = nullptr;
     RhsState *h_st_ = nullptr;       // res_->h_st
-    BatchState *h_batch_ = nullptr;  // res_->h_batch
     std::deque<Pending> pending_;
     int next_slot_ = 0;
     int phase_ = 0;  // 0 running, 1 finishing, 2 done

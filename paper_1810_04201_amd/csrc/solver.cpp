@@ -48,8 +48,7 @@ Solve::Solve(wd_lattice *lat, const wd_solve_params &p, const double *b, double 
 }
 
 int SlotRes::create() {
-    if (hipHostMalloc((void **)&h_st, sizeof(RhsState) * kSlots * 12) != hipSuccess ||
-        hipHostMalloc((void **)&h_batch, sizeof(BatchState) * kSlots) != hipSuccess)
+    if (hipHostMalloc((void **)&h_st, sizeof(RhsState) * kSlots * 12) != hipSuccess)
         return fail(WD_ERR_NOMEM, "pinned host allocation failed");
     for (int i = 0; i < kSlots; ++i)
         if (hipEventCreateWithFlags(&ev[i], hipEventDisableTiming) != hipSuccess)
@@ -64,7 +63,6 @@ void SlotRes::destroy() {
         if (ev[i]) (void)hipEventDestroy(ev[i]);
     if (final_ev) (void)hipEventDestroy(final_ev);
     if (h_st) (void)hipHostFree(h_st);
-    if (h_batch) (void)hipHostFree(h_batch);
     *this = SlotRes{};
 }
 
@@ -119,6 +117,19 @@ static bool fused_iteration(const wd_lattice *lat, const wd_solve_params &p) {
                                (int)reduce_partials_cap(lat->g, p.nrhs));
 }
 
+// partials per rhs of an iteration's reductions where the kernels that need
+// them finish them (Cons), 0 where k_finalize does
+static int deferred_partials(const wd_lattice *lat, const wd_solve_params &p) {
+    if (!fused_iteration(lat, p)) return 0;
+    int nb = 0, threads = 0;
+    if (p.form & WD_SOLVE_EVEN_ODD)
+        hop_half_partials(lat->g, p.prec_inner, p.nrhs, &nb, &threads);
+    else
+        dslash_partials(lat->g, p.prec_inner, p.nrhs, &nb, &threads);
+    if (threads > kSiteBlock) threads = kSiteBlock;  // the x and p update's
+    return nb <= kDeferLoads * threads ? nb : 0;
+}
+
 size_t Solve::footprint(const wd_lattice *lat, const wd_solve_params &p) {
     const bool eo = (p.form & WD_SOLVE_EVEN_ODD) != 0;
     const int V = eo ? lat->g.V / 2 : lat->g.V, nr = p.nrhs;
@@ -131,7 +142,8 @@ size_t Solve::footprint(const wd_lattice *lat, const wd_solve_params &p) {
     const int nlo = 2 + (fused_iteration(lat, p) ? 0 : 1) + (eo ? 1 : 0);
     b += 2 * field_bytes(lo_xr, V, nr) + nlo * field_bytes(lo, V, nr);
     b += align256((size_t)reduce_partials_cap(lat->g, p.nrhs) * sizeof(double));
-    b += align256(sizeof(RhsState) * 12) + 256;
+    b += align256((size_t)deferred_partials(lat, p) * p.nrhs * sizeof(double));
+    b += 2 * align256(sizeof(RhsState) * 12);
     return b;
 }
 
@@ -190,10 +202,13 @@ int Solve::setup(hipStream_t stream, SlotRes *res) {
     partials_ = (double *)cur;
     partials_cap_ = (int)reduce_partials_cap(lat_->g, nrhs);
     cur += align256((size_t)partials_cap_ * sizeof(double));
+    defer_ = deferred_partials(lat_, p_);
+    partials2_ = (double *)cur;
+    cur += align256((size_t)defer_ * nrhs * sizeof(double));
     st_ = (RhsState *)cur;
     cur += align256(sizeof(RhsState) * 12);
-    batch_ = (BatchState *)cur;
-    cur += 256;
+    st2_ = (RhsState *)cur;
+    cur += align256(sizeof(RhsState) * 12);
     if ((size_t)(cur - base) > bytes_) return fail(WD_ERR_STATE, "workspace layout overflow");
 
     if (!res) {
@@ -203,7 +218,6 @@ int Solve::setup(hipStream_t stream, SlotRes *res) {
     }
     res_ = res;
     h_st_ = res->h_st;
-    h_batch_ = res->h_batch;
     final_ev_ = res->final_ev;
 
     ctl_.tol2 = p_.tol * p_.tol;
@@ -224,9 +238,14 @@ int Solve::setup(hipStream_t stream, SlotRes *res) {
         return v < 4 ? 4 : v;
     }();
     chunk_ = site_iters < 4 ? 4 : (site_iters > chunk_max ? chunk_max : (int)site_iters);
-    // a gated reliable update after every iteration on large lattices (its
-    // launches cost nothing next to an iteration), every 4 on small ones
-    rel_every_ = n >= (1 << 20) ? 1 : 4;
+    // A gated reliable update costs six to eight launches that do nothing (1.3
+    // us each on 4^4, 5-8 us on the grids of large lattices), a frozen rhs that
+    // waits for the next one three to five such launches an iteration.  Mixed
+    // solves take an update every 10 to 15 iterations: the sum is least near
+    // every 4 on large lattices (48^3 x 96 binary16 even-odd: 47 us of a 2.03
+    // ms iteration with one after each) and every 8 on small ones; plain
+    // float64 needs only the one that ends it, once a chunk.
+    rel_every_ = !ctl_.mixed ? chunk_ : (n >= (1 << 20) ? 4 : 8);
     // chunks replayed from a captured HIP graph: cuts the host's launch work,
     // which bounds a server driving many small solves from one thread
     // (measured 113 -> 182 solves/s on 8^4 / 12^4 requests).  Needs a stream
@@ -243,7 +262,6 @@ RedArgs Solve::red(int mode) const {
     r.partials = partials_;
     r.partials_cap = partials_cap_;
     r.st = st_;
-    r.batch = batch_;
     r.ctl = ctl_;
     r.mode = mode;
     return r;
@@ -269,9 +287,8 @@ void Solve::op(bool first, const FieldRef &in, const FieldRef &out, const RedArg
 
 // The second operator application of an iteration on in = A p, with the
 // r update fused into its last launch; false if nothing was launched
-bool Solve::op_xr(const FieldRef &in, const RedArgs &rr, Gate gate) {
+bool Solve::op_xr(const FieldRef &in, const XrArgs &xr, const RedArgs &rr, Gate gate) {
     const double k = p_.kappa;
-    const XrArgs xr{rl_};
     if (!eo_) return dslash_xr(lat_, gauge_lo_, k, d2_, in, xr, rr, gate, s_);
     hop_half(lat_, ghlo_, 1, k, 0.0, d2_, in, FieldRef{}, tmpl_, nullptr, gate, s_);
     hop_half_xr(lat_, ghlo_, 0, -k, 1.0, d2_, tmpl_, in, xr, rr, gate, s_);
@@ -280,8 +297,8 @@ bool Solve::op_xr(const FieldRef &in, const RedArgs &rr, Gate gate) {
 
 int Solve::start() {
     const double k = p_.kappa;
-    const Gate none{nullptr, nullptr, GATE_ACTIVE};
-    launch_init_state(st_, batch_, p_.nrhs, s_);
+    const Gate none{nullptr, 0, GATE_ACTIVE};
+    launch_init_state(st_, st2_, p_.nrhs, s_);
     RedArgs rb = red(RED_B0);
     // b' = A^dag b^ (CGNR) or b^ (CGNE), |b'|^2; b^ = b, or b_e - D_eo b_o
     FieldRef bh = b64_;
@@ -310,12 +327,11 @@ int Solve::start() {
     if (p_.x0_given) {
         enqueue_reliable();
     } else {
-        const Gate trig{st_, batch_, GATE_TRIGGER};
-        const Gate rst{st_, batch_, GATE_RESTART};
+        const Gate trig{st_, p_.nrhs, GATE_TRIGGER};
+        const Gate rst{st_, p_.nrhs, GATE_RESTART};
         RedArgs rt = red(RED_TRUE);
         launch_residual(r64_, bp_, FieldRef{}, rt, trig, s_);  // x = 0: r = b'
-        launch_convert(r64_, rl_, rst, s_);
-        launch_restart_p(pl_, rl_, rst, s_);
+        launch_restart(r64_, rl_, pl_, rst, s_);
     }
     if (launch_failed()) return fail(WD_ERR_HIP, "kernel launch failed");
     return push_status();
@@ -325,12 +341,23 @@ void Solve::enqueue_inner(int iters) {
     const Gate g = gate();
     RedArgs ra = red(RED_ALPHA);
     RedArgs rr = red(RED_RR);
+    // the two reductions finished by the kernels that need them: state st_
+    // -> st2_ in the r update, st2_ -> st_ in the x and p update
+    Cons calpha{partials_, 0, st_, st2_}, crr{};
+    if (defer_) {
+        ra.deferred = rr.deferred = true;
+        rr.partials = partials2_;
+        rr.partials_cap = defer_ * p_.nrhs;
+        calpha = Cons{partials_, defer_, st_, st2_};
+        crr = Cons{partials2_, defer_, st2_, st_};
+    }
+    const XrArgs xr{rl_, calpha, ctl_};
     for (int i = 0; i < iters; ++i) {
         op(true, pl_, tl_, &ra, g, true);
         if (fuse_xr_) {
             // r updated where A p is formed; x += alpha p with the p update
-            op_xr(tl_, rr, g);
-            launch_update_xp(xl_, pl_, rl_, g, s_);
+            op_xr(tl_, xr, rr, g);
+            launch_update_xp(xl_, pl_, rl_, g, crr, ctl_, s_);
         } else {
             op(false, tl_, apl_, nullptr, g, true);
             launch_update_xr(xl_, rl_, pl_, apl_, rr, g, s_);
@@ -374,21 +401,20 @@ int Solve::enqueue_chunk() {
 // unfinished rhs is frozen and at least one waits for it; then it takes the
 // waiting rhs, and resets r_lo and p of those it restarts (GATE_RESTART).
 void Solve::enqueue_reliable() {
-    const Gate trig{st_, batch_, GATE_TRIGGER};
-    const Gate rst{st_, batch_, GATE_RESTART};
+    const Gate trig{st_, p_.nrhs, GATE_TRIGGER};
+    const Gate rst{st_, p_.nrhs, GATE_RESTART};
     RedArgs rt = red(RED_TRUE);
     launch_accum_zero(x64_, xl_, pl_, trig, s_);
     op(true, x64_, t64_, nullptr, trig, false);
     op(false, t64_, ax64_, nullptr, trig, false);
     launch_residual(r64_, bp_, ax64_, rt, trig, s_);
-    launch_convert(r64_, rl_, rst, s_);
-    launch_restart_p(pl_, rl_, rst, s_);
+    launch_restart(r64_, rl_, pl_, rst, s_);
 }
 
 void Solve::enqueue_finish() {
     const double k = p_.kappa;
-    const Gate none{nullptr, nullptr, GATE_ACTIVE};
-    launch_accum_zero(x64_, xl_, pl_, Gate{st_, nullptr, GATE_ACTIVE}, s_);  // unconverged rhs
+    const Gate none{nullptr, 0, GATE_ACTIVE};
+    launch_accum_zero(x64_, xl_, pl_, gate(), s_);  // unconverged rhs
     RedArgs ra = red(RED_AUX);
     RedArgs ra2 = red(RED_AUX_ADD);
     RedArgs rb = red(RED_AUX2);
@@ -429,8 +455,6 @@ int Solve::push_status() {
     RhsState *hs = h_st_ + (size_t)slot * p_.nrhs;
     if (hipMemcpyAsync(hs, st_, sizeof(RhsState) * p_.nrhs, hipMemcpyDeviceToHost, s_) !=
             hipSuccess ||
-        hipMemcpyAsync(h_batch_ + slot, batch_, sizeof(BatchState), hipMemcpyDeviceToHost, s_) !=
-            hipSuccess ||
         hipEventRecord(res_->ev[slot], s_) != hipSuccess)
         return fail(WD_ERR_HIP, "status copy failed");
     pending_.push_back(Pending{res_->ev[slot], slot});
@@ -470,10 +494,12 @@ int Solve::advance(bool block) {
         if (e != hipSuccess) return fail(WD_ERR_HIP, "solve failed on the device: %s",
                                          hipGetErrorString(e));
         pending_.pop_front();
-        const BatchState &bs = h_batch_[f.slot];
         // still iterating, or frozen rhs that the next gated reliable update
         // (already in the stream) will take
-        if (bs.n_active > 0 || bs.n_trigger > 0) continue;
+        const RhsState *hs = h_st_ + (size_t)f.slot * p_.nrhs;
+        bool more = false;
+        for (int r = 0; r < p_.nrhs; ++r) more |= hs[r].active || hs[r].trigger;
+        if (more) continue;
         // every rhs converged or failed: pending inner chunks are no-ops
         enqueue_finish();
         if (launch_failed()) return fail(WD_ERR_HIP, "kernel launch failed");

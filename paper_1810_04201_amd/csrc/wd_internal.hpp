@@ -250,29 +250,45 @@ struct RhsState {
                      // with alpha p not yet in x_lo: the reliable update adds it
 };
 
-struct BatchState {
-    int n_active;   // rhs still iterating (grid-uniform early-exit flag)
-    int n_trigger;  // rhs frozen and waiting for a reliable update
-    int n_done;     // rhs converged or failed
-    int pad;
+struct SolveCtl {
+    double tol2;      // tol^2: converged when rr <= tol2 * rr0
+    double delta2;    // reliable trigger when rr < delta2 * rr_max
+    int max_iter;
+    int max_inner;    // reliable update at least every max_inner iterations (0: never)
+    int nrhs;
+    int mixed;        // 1: inner iterations in low precision
+    int lag_x;        // 1: x += alpha p is done by the next p update (the
+                      // stencil that forms A p only updates r)
 };
 
-// Optional gating of a kernel on the solver state, uniform over the launch
-// (batch) and over a workgroup (rhs):
-//   GATE_ACTIVE   inner iterations: off when no rhs is iterating; rhs with
-//                 active != 0.
+// Optional gating of a kernel on the solver state, uniform over a workgroup
+// (its rhs) and, for reliable updates, over the launch:
+//   GATE_ACTIVE   inner iterations: rhs with active != 0.
 //   GATE_TRIGGER  a reliable update: off unless every unfinished rhs is
-//                 frozen and at least one waits for it; rhs with trigger set
-//                 (not converged).
+//                 frozen and at least one waits for it (read from the states
+//                 of all nrhs); rhs with trigger set (not converged).
 //   GATE_RESTART  the reset of r_lo and p after a reliable update: rhs the
 //                 update restarted.
-// batch == nullptr: no batch test; st == nullptr: every rhs.
+// st == nullptr: every rhs.
 enum GateMode { GATE_ACTIVE = 0, GATE_TRIGGER = 1, GATE_RESTART = 2 };
 
 struct Gate {
     const RhsState *st;
-    const BatchState *batch;
+    int nrhs;
     int mode;
+};
+
+// The reduction of the launch before, finished by the kernel that needs its
+// result: each workgroup sums the nb partials of its rhs and steps the state
+// from `from`; one of them writes it to `next` (the two differ, so that a
+// workgroup that starts late still reads the old state).  An iteration steps
+// the state twice, st -> st2 in the r update and st2 -> st in the x and p
+// update.  nb == 0: a launch of k_finalize did it, and the state is the gate's.
+struct Cons {
+    const double *part;
+    int nb;
+    const RhsState *from;
+    RhsState *next;
 };
 
 // Halo exchange for a lattice that is one t-slab of a larger one (one slab
@@ -293,6 +309,8 @@ struct Gate {
 // then follows in the p update (launch_update_xp)
 struct XrArgs {
     FieldRef r;
+    Cons alpha;  // |A p|^2, if this kernel finishes it
+    SolveCtl ctl;
 };
 
 struct Halo {
@@ -304,17 +322,6 @@ struct Halo {
     // the launch's k-th chunk (all chunks: 0, 1); region selects them in
     // launch_dslash_halo (0 all, 1 interior, 2 the two holding the slab ends)
     int region, cfirst, cstep;
-};
-
-struct SolveCtl {
-    double tol2;      // tol^2: converged when rr <= tol2 * rr0
-    double delta2;    // reliable trigger when rr < delta2 * rr_max
-    int max_iter;
-    int max_inner;    // reliable update at least every max_inner iterations (0: never)
-    int nrhs;
-    int mixed;        // 1: inner iterations in low precision
-    int lag_x;        // 1: x += alpha p is done by the next p update (the
-                      // stencil that forms A p only updates r)
 };
 
 enum RedMode {
@@ -333,9 +340,10 @@ struct RedArgs {
     double *partials;    // partials_cap doubles (one per block and rhs)
     int partials_cap;    // launchers never use more blocks * nrhs than this
     RhsState *st;        // nrhs entries
-    BatchState *batch;
     SolveCtl ctl;
     int mode;
+    // the next kernel finishes the reduction (see Cons): no k_finalize
+    bool deferred;
 };
 
 inline int blocks_for(int64_t n, int bs) { return (int)((n + bs - 1) / bs); }
@@ -354,6 +362,10 @@ inline int blocks_for(int64_t n, int bs) { return (int)((n + bs - 1) / bs); }
 constexpr int kSiteBlock = 256;
 
 inline int site_blocks(int V) { return blocks_for(V, kSiteBlock); }
+
+// partials that a thread takes of a reduction which the next kernel finishes
+// (Cons): 1024 a workgroup of 256
+constexpr int kDeferLoads = 4;
 
 // largest workgroup (part of a brick slice) of the time-marching stencil
 #ifndef WD_TM_MAXB
@@ -598,8 +610,6 @@ void launch_su3_check(const void *g64, int V, unsigned long long *maxbits, hipSt
 // canonical [rhs][V][12] float64 <-> field (format conversion + reorder)
 void launch_import(const double *canon, FieldRef f, const Geom &g, hipStream_t s);
 void launch_export(FieldRef f, double *canon, const Geom &g, hipStream_t s);
-// dst = src with a format conversion (same nrhs); gated rhs only
-void launch_convert(FieldRef src, FieldRef dst, Gate gate, hipStream_t s);
 void launch_zero(FieldRef f, hipStream_t s);
 // even-odd halves (V / 2 sites each, parity p): links of the parity-p sites
 // from the F64-18 tiles, in the half layout and link form `form`
@@ -668,6 +678,10 @@ bool launch_dslash_xr(const Geom &g, const void *gauge, double kappa, int dagger
                       const XrArgs &xr, const RedArgs &red, Gate gate, hipStream_t s,
                       const void *g12 = nullptr);
 bool dslash_xr_supported(const Geom &g, int prec, int nrhs, int partials_cap);
+// partials per rhs of a solve's reducing stencils (full lattice; even-odd), and
+// the threads of their workgroups
+void dslash_partials(const Geom &g, int prec, int nrhs, int *nb, int *threads);
+void hop_half_partials(const Geom &g, int prec, int nrhs, int *nb, int *threads);
 
 // x += alpha p ; r -= alpha Ap ; reduce |r|^2 (red.mode = RED_RR); active rhs
 void launch_update_xr(FieldRef x, FieldRef r, FieldRef p, FieldRef Ap, const RedArgs &red,
@@ -675,21 +689,21 @@ void launch_update_xr(FieldRef x, FieldRef r, FieldRef p, FieldRef Ap, const Red
 // p = r + beta p for active rhs
 void launch_update_p(FieldRef p, FieldRef r, Gate gate, hipStream_t s);
 // x += alpha p ; p = r + beta p (active rhs): the x update lagged behind the
-// r update of a stencil with XrArgs
-void launch_update_xp(FieldRef x, FieldRef p, FieldRef r, Gate gate, hipStream_t s);
+// r update of a stencil with XrArgs, whose |r|^2 it finishes if rr.nb
+void launch_update_xp(FieldRef x, FieldRef p, FieldRef r, Gate gate, const Cons &rr,
+                      const SolveCtl &ctl, hipStream_t s);
 // r = b - Ax (Ax.data == nullptr: r = b) in float64, reduce |r|^2 with red.mode
 void launch_residual(FieldRef r, FieldRef b, FieldRef Ax, const RedArgs &red, Gate gate,
                      hipStream_t s);
 // reduce |f|^2 (any precision) with red.mode
 void launch_norm(FieldRef f, const RedArgs &red, hipStream_t s);
-// phase 2 of a reduction: one block sums the nb per-block partials in a fixed
-// order and runs the finaliser; gate_mode >= 0: skipped when the producing
-// kernel's batch gate (GateMode) was off, -1: always runs
-void launch_finalize(const RedArgs &red, int nb, int gate_mode, hipStream_t s);
-// zero the states and the batch counters
-void launch_init_state(RhsState *st, BatchState *batch, int nrhs, hipStream_t s);
-// after a reliable update, for the rhs it restarted (gate GATE_RESTART):
-// p = r at the first update, p = r + beta p afterwards
-void launch_restart_p(FieldRef p, FieldRef r, Gate gate, hipStream_t s);
+// phase 2 of a reduction over nb partials per rhs (nothing if it is deferred):
+// a block per rhs sums them in a fixed order and runs the finaliser
+void launch_finalize(const RedArgs &red, int nb, hipStream_t s);
+// zero the states
+void launch_init_state(RhsState *st, RhsState *st2, int nrhs, hipStream_t s);
+// after a reliable update, for the rhs it restarted (gate GATE_RESTART): r_lo =
+// r64, and p = r_lo at the first update, p = r_lo + beta p afterwards
+void launch_restart(FieldRef r64, FieldRef rlo, FieldRef p, Gate gate, hipStream_t s);
 
 }  // namespace wd
