@@ -65,22 +65,58 @@ void launch_finalize(const RedArgs &red, int nb, hipStream_t s) {
 
 // ------------------------------------------------------------------ gauge
 
-// canonical [s][mu][a][b][re,im] (lexicographic s) -> F64-18 tiles in brick order
-__global__ void k_pack_gauge_f64(const double2 *__restrict__ canon, void *__restrict__ g, Geom geo) {
+// Gauge ingest: canonical [s][mu][a][b][re,im] (lexicographic s) -> F64-18 tiles
+// in brick order, and in the same pass (CHECK) the F64-12 tiles (g12 given) and
+// the largest deviation of a row 2 from conj(row 0 x row 1): per block in LDS,
+// then one atomic maximum on the bit pattern (non-negative doubles order like
+// their patterns).  Bound by memory: 1536 bytes per site where a pass each for
+// the tiles, the check and the 12-real form moved 2688 (24^3 x 48: 168 + 98 + 82
+// us, in one pass 213).
+template <bool CHECK>
+__global__ void __launch_bounds__(kBS) k_ingest(const double2 *__restrict__ canon,
+                                                void *__restrict__ g, void *__restrict__ g12,
+                                                Geom geo, unsigned long long *maxbits) {
+    __shared__ double wmax[kBS / 64];
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= geo.V) return;
-    int x, y, z, t;
-    coords_of(geo, i, x, y, z, t);
-    const double2 *src = canon + (size_t)lex_of(geo, x, y, z, t) * 36;
+    double e = 0.0;
+    if (i < geo.V) {
+        int x, y, z, t;
+        coords_of(geo, i, x, y, z, t);
+        const double2 *src = canon + (size_t)lex_of(geo, x, y, z, t) * 36;
 #pragma unroll
-    for (int mu = 0; mu < 4; ++mu) {
-        cx<double> u[9];
+        for (int mu = 0; mu < 4; ++mu) {
+            cx<double> u[9];
 #pragma unroll
-        for (int k = 0; k < 9; ++k) {
-            double2 d = src[mu * 9 + k];
-            u[k] = {d.x, d.y};
+            for (int k = 0; k < 9; ++k) {
+                double2 d = src[mu * 9 + k];
+                u[k] = {d.x, d.y};
+            }
+            Link<WD_F64>::store(g, mu, i, u);
+            if constexpr (CHECK) {
+                if (g12) Link<kLinkF64R12>::store(g12, mu, i, u);
+                cx<double> r[9];
+#pragma unroll
+                for (int k = 0; k < 6; ++k) r[k] = u[k];
+                reconstruct_row2(r);
+#pragma unroll
+                for (int j = 6; j < 9; ++j) {
+                    const double dr = u[j].re - r[j].re, di = u[j].im - r[j].im;
+                    const double d = sqrt(dr * dr + di * di);
+                    if (!(d <= e)) e = d == d ? d : INFINITY;
+                }
+            }
         }
-        Link<WD_F64>::store(g, mu, i, u);
+    }
+    if constexpr (CHECK) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) e = fmax(e, __shfl_xor(e, off, 64));
+        if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = e;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            double m = wmax[0];
+            for (int w = 1; w < (int)(blockDim.x >> 6); ++w) m = fmax(m, wmax[w]);
+            atomicMax(maxbits, (unsigned long long)__double_as_longlong(m));
+        }
     }
 }
 
@@ -98,9 +134,15 @@ __global__ void k_gauge_lo(const void *__restrict__ g, void *__restrict__ o, int
     }
 }
 
-void launch_pack_gauge_f64(const double *canon, void *g64, const Geom &geo, hipStream_t s) {
-    hipLaunchKernelGGL(k_pack_gauge_f64, dim3(blocks_for(geo.V, kBS)), dim3(kBS), 0, s,
-                       (const double2 *)canon, g64, geo);
+void launch_ingest(const double *canon, void *g64, void *g12, unsigned long long *maxbits,
+                   const Geom &geo, hipStream_t s) {
+    const dim3 gr(blocks_for(geo.V, kBS)), bs(kBS);
+    if (maxbits)
+        hipLaunchKernelGGL(k_ingest<true>, gr, bs, 0, s, (const double2 *)canon, g64, g12, geo,
+                           maxbits);
+    else
+        hipLaunchKernelGGL(k_ingest<false>, gr, bs, 0, s, (const double2 *)canon, g64, nullptr,
+                           geo, maxbits);
 }
 
 void launch_gauge_lo(const void *g64, void *glo, int form, int V, hipStream_t s) {
@@ -111,47 +153,6 @@ void launch_gauge_lo(const void *g64, void *glo, int form, int V, hipStream_t s)
         hipLaunchKernelGGL(k_gauge_lo<WD_F16>, gr, bs, 0, s, g64, glo, V);
     else if (form == kLinkF16R8)
         hipLaunchKernelGGL(k_gauge_lo<kLinkF16R8>, gr, bs, 0, s, g64, glo, V);
-    else
-        hipLaunchKernelGGL(k_gauge_lo<kLinkF64R12>, gr, bs, 0, s, g64, glo, V);
-}
-
-// Largest deviation of a stored row 2 from conj(row 0 x row 1): per block in
-// LDS, then one atomic maximum on the bit pattern (non-negative doubles
-// order like their patterns)
-__global__ void __launch_bounds__(256) k_su3_check(const void *__restrict__ g, int V,
-                                                   unsigned long long *maxbits) {
-    __shared__ double wmax[256 / 64];
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    double e = 0.0;
-    if (i < V) {
-#pragma unroll
-        for (int mu = 0; mu < 4; ++mu) {
-            cx<double> u[9], r[9];
-            Link<WD_F64>::load(g, mu, i, u);
-#pragma unroll
-            for (int k = 0; k < 6; ++k) r[k] = u[k];
-            reconstruct_row2(r);
-#pragma unroll
-            for (int j = 6; j < 9; ++j) {
-                const double dr = u[j].re - r[j].re, di = u[j].im - r[j].im;
-                const double d = sqrt(dr * dr + di * di);
-                if (!(d <= e)) e = d == d ? d : INFINITY;
-            }
-        }
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) e = fmax(e, __shfl_xor(e, off, 64));
-    if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = e;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double m = wmax[0];
-        for (int w = 1; w < (int)(blockDim.x >> 6); ++w) m = fmax(m, wmax[w]);
-        atomicMax(maxbits, (unsigned long long)__double_as_longlong(m));
-    }
-}
-
-void launch_su3_check(const void *g64, int V, unsigned long long *maxbits, hipStream_t s) {
-    hipLaunchKernelGGL(k_su3_check, dim3(blocks_for(V, 256)), dim3(256), 0, s, g64, V, maxbits);
 }
 
 // even-odd: links of the parity-p sites in the half layout and format PREC
@@ -403,8 +404,8 @@ __global__ void k_update_p(FieldRef p, FieldRef r, Gate gate) {
     const int rhs = blockIdx.y;
     if (!gate_rhs(gate, rhs)) return;
     using R = typename Spinor<PX>::R;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
     using RP = typename Spinor<PPP>::R;
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= p.V) return;
     const FieldRef pf = rhs_view(p, rhs);
     const R beta = (R)gate.st[rhs].beta;

@@ -395,51 +395,55 @@ int wd_set_gauge(wd_lattice *lat, const double *U, void *stream) {
     // every resident form is rebuilt below; until all of them hold the new
     // links (an early error return leaves them mixed) the lattice has none
     lat->has_gauge = false;
+    const size_t bytes18 = gauge_bytes(WD_F64, lat->g.V);
     if (!lat->gauge[WD_F64]) {
+        // (and a word behind the tiles for the deviation found on ingest)
         void *p = nullptr;
-        hipError_t he = hipMalloc(&p, gauge_bytes(WD_F64, lat->g.V));
+        hipError_t he = hipMalloc(&p, bytes18 + 256);
         if (he != hipSuccess)
             return fail(WD_ERR_NOMEM, "hipMalloc of the F64 gauge form failed: %s",
                         hipGetErrorString(he));
         lat->gauge[WD_F64] = p;
     }
-    launch_pack_gauge_f64(U, lat->gauge[WD_F64], lat->g, s);
     // float64 links also stored as 12 reals when every link is special
     // unitary to rounding (the marching stencil then reads 384 instead of
-    // 576 link bytes per site); WD_LINKS64_12=0 keeps 18 reals only
+    // 576 link bytes per site); WD_LINKS64_12=0 keeps 18 reals only.  The form
+    // is written along with the other, and dropped if the check then says no;
+    // without memory for it the lattice keeps 18 reals only.
     const char *e12 = getenv("WD_LINKS64_12");
     const bool want12 = !(e12 && atoi(e12) == 0);
-    lat->su3_dev = -1.0;
-    if (want12) {
-        unsigned long long *dm = nullptr, hm = 0;
-        WD_HIP_CHECK(hipMallocAsync((void **)&dm, sizeof(hm), s));
-        (void)hipMemsetAsync(dm, 0, sizeof(hm), s);
-        launch_su3_check(lat->gauge[WD_F64], lat->g.V, dm, s);
-        (void)hipMemcpyAsync(&hm, dm, sizeof(hm), hipMemcpyDeviceToHost, s);
-        (void)hipFreeAsync(dm, s);
-        WD_LAUNCH_CHECK();
-        WD_HIP_CHECK(hipStreamSynchronize(s));
-        double dev;
-        memcpy(&dev, &hm, sizeof(dev));
-        lat->su3_dev = dev;
-    }
-    if (want12 && lat->su3_dev <= kSu3Tol && !lat->gauge12) {
-        // without memory for it the lattice keeps 18 reals only
-        void *p = nullptr;
-        if (hipMalloc(&p, gauge_bytes(kLinkF64R12, lat->g.V)) == hipSuccess)
-            lat->gauge12 = p;
-        else
-            (void)hipGetLastError();
-    }
-    if (want12 && lat->su3_dev <= kSu3Tol && lat->gauge12) {
-        launch_gauge_lo(lat->gauge[WD_F64], lat->gauge12, kLinkF64R12, lat->g.V, s);
-    } else if (lat->gauge12) {
-        (void)hipFree(lat->gauge12);
+    auto drop12 = [&] {
+        if (lat->gauge12) (void)hipFree(lat->gauge12);
         lat->gauge12 = nullptr;
+    };
+    lat->su3_dev = -1.0;
+    unsigned long long hm = 0, *dm = nullptr;
+    if (want12) {
+        if (!lat->gauge12) {
+            void *p = nullptr;
+            if (hipMalloc(&p, gauge_bytes(kLinkF64R12, lat->g.V)) == hipSuccess)
+                lat->gauge12 = p;
+            else
+                (void)hipGetLastError();
+        }
+        dm = (unsigned long long *)((char *)lat->gauge[WD_F64] + bytes18);
+        (void)hipMemsetAsync(dm, 0, sizeof(hm), s);
     }
+    launch_ingest(U, lat->gauge[WD_F64], want12 ? lat->gauge12 : nullptr, dm, lat->g, s);
+    if (want12) (void)hipMemcpyAsync(&hm, dm, sizeof(hm), hipMemcpyDeviceToHost, s);
     for (int p = 1; p < 3; ++p)
         if (lat->gauge[p])
             launch_gauge_lo(lat->gauge[WD_F64], lat->gauge[p], link_form(lat->g, p), lat->g.V, s);
+    WD_LAUNCH_CHECK();
+    WD_HIP_CHECK(hipStreamSynchronize(s));
+    if (want12) {
+        double dev;
+        memcpy(&dev, &hm, sizeof(dev));
+        lat->su3_dev = dev;
+        if (!(dev <= kSu3Tol)) drop12();
+    } else {
+        drop12();
+    }
     // float64 halves whose form no longer matches are dropped (rebuilt on use)
     if (lat->gauge_eo[WD_F64][0] && lat->eo64_r12 != (lat->gauge12 != nullptr)) {
         for (int q = 0; q < 2; ++q) {
@@ -447,15 +451,18 @@ int wd_set_gauge(wd_lattice *lat, const double *U, void *stream) {
             lat->gauge_eo[WD_F64][q] = nullptr;
         }
     }
+    bool halves = false;
     for (int p = 0; p < 3; ++p)
         for (int q = 0; q < 2; ++q)
-            if (lat->gauge_eo[p][q])
+            if (lat->gauge_eo[p][q]) {
+                halves = true;
                 launch_gauge_split(lat->gauge[WD_F64], lat->gauge_eo[p][q],
                                    p == WD_F64 && lat->eo64_r12 ? kLinkF64R12
                                                                 : link_form(lat->g, p),
                                    q, lat->g, s);
+            }
     WD_LAUNCH_CHECK();
-    WD_HIP_CHECK(hipStreamSynchronize(s));
+    if (halves) WD_HIP_CHECK(hipStreamSynchronize(s));
     lat->has_gauge = true;
     return WD_OK;
 }

@@ -598,14 +598,14 @@ inline void choose_bricks(Geom &g) {
 // ------------------------------------------------------------------ launchers
 // (defined in the .hip files; all stream-ordered, no host synchronisation)
 
-// canonical float64 links -> F64-18 tiles (brick order)
-void launch_pack_gauge_f64(const double *canon, void *g64, const Geom &g, hipStream_t s);
-// F64-18 tiles -> 12-real F32, F16 or F64 (form kLinkF64R12) tiles
+// canonical float64 links -> F64-18 tiles (brick order).  With maxbits, in the
+// same pass: *maxbits = max(*maxbits, largest |row 2 - conj(row 0 x row 1)| of a
+// link) as the bit pattern of a non-negative double (NaN counts as infinity;
+// *maxbits must be set beforehand), and the F64-12 tiles where g12 is given
+void launch_ingest(const double *canon, void *g64, void *g12, unsigned long long *maxbits,
+                   const Geom &g, hipStream_t s);
+// F64-18 tiles -> 12-real F32 or F16 tiles, or the 8-real F16 ones
 void launch_gauge_lo(const void *g64, void *glo, int form, int V, hipStream_t s);
-// *maxbits = max(*maxbits, largest |row 2 - conj(row 0 x row 1)| over the
-// F64-18 links) as the bit pattern of a non-negative double (NaN counts as
-// infinity); *maxbits must be set beforehand
-void launch_su3_check(const void *g64, int V, unsigned long long *maxbits, hipStream_t s);
 
 // canonical [rhs][V][12] float64 <-> field (format conversion + reorder)
 void launch_import(const double *canon, FieldRef f, const Geom &g, hipStream_t s);
