@@ -242,19 +242,48 @@ __global__ void k_export(FieldRef f, double2 *__restrict__ canon, Geom geo) {
 }
 
 // canonical [rhs][s][12] <-> half field of parity p (entry h: site
-// site_of_half(h, p)); f.V = V / 2
-template <int PREC>
-__global__ void k_import_half(const double2 *__restrict__ canon, FieldRef f, int p, Geom geo) {
+// site_of_half(h, p)); f.V = V / 2.  A wave's 64 sites come in through LDS, 12
+// lanes to a site (208 bytes apart there, so that the lanes that then read a
+// component of one site each meet different banks): a lane reading its own site
+// spreads every load over 64 places 384 bytes apart (30^3 x 60
+// into float32: 90 us, this way 64).  DIRECT does so:
+// buffers aligned to a double only.
+template <int PREC, bool DIRECT>
+__global__ void __launch_bounds__(kSiteBlock) k_import_half(const double2 *__restrict__ canon,
+                                                            FieldRef f, int p, Geom geo) {
+    typedef __attribute__((address_space(3))) void lds_void;
+    __shared__ __align__(16) char img[kSiteBlock / 64][DIRECT ? 16 : 64 * 208];
     const int h = blockIdx.x * blockDim.x + threadIdx.x;
-    if (h >= f.V) return;
+    const bool mine = h < f.V;
     const int r = blockIdx.y;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int x, y, z, t;
-    coords_of(geo, site_of_half(geo, h, p), x, y, z, t);
-    const double2 *src = canon + ((size_t)r * geo.V + lex_of(geo, x, y, z, t)) * 12;
+    coords_of(geo, site_of_half(geo, mine ? h : f.V - 1, p), x, y, z, t);
+    const int lex = lex_of(geo, x, y, z, t);
+    const double2 *src = canon + (size_t)r * geo.V * 12;
     cx<double> v[12];
+    if constexpr (DIRECT) {
+        if (!mine) return;
+        src += (size_t)lex * 12;
+#pragma unroll
+        for (int k = 0; k < 12; ++k) v[k] = {src[k].x, src[k].y};
+        store_from_double<PREC>(rhs_view(f, r), h, v);
+        return;
+    }
+#pragma unroll
+    for (int j = 0; j < 13; ++j) {
+        const int e = j * 64 + lane, site = e / 13, k = e - site * 13;
+        const size_t from = (size_t)__shfl(lex, site, 64) * 12 + (k < 12 ? k : 11);
+        __builtin_amdgcn_global_load_lds((const void *)(src + from),
+                                         (lds_void *)(img[w] + j * 1024), 16, 0, 0);
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("" ::: "memory");
+    if (!mine) return;
 #pragma unroll
     for (int k = 0; k < 12; ++k) {
-        double2 d = src[k];
+        const d2_t d = *(const d2_t *)(img[w] + lane * 208 + k * 16);
         v[k] = {d.x, d.y};
     }
     store_from_double<PREC>(rhs_view(f, r), h, v);
@@ -339,8 +368,14 @@ void launch_export(FieldRef f, double *canon, const Geom &geo, hipStream_t s) {
 }
 
 void launch_import_half(const double *canon, FieldRef f, int p, const Geom &geo, hipStream_t s) {
-    WD_DISPATCH_PREC(f.prec, hipLaunchKernelGGL(k_import_half<PP>, field_grid(f), dim3(kSiteBlock),
-                                                0, s, (const double2 *)canon, f, p, geo));
+    const dim3 gr = field_grid(f), bs(kSiteBlock);
+    if (((uintptr_t)canon & 15) == 0) {
+        WD_DISPATCH_PREC(f.prec, hipLaunchKernelGGL((k_import_half<PP, false>), gr, bs, 0, s,
+                                                    (const double2 *)canon, f, p, geo));
+    } else {
+        WD_DISPATCH_PREC(f.prec, hipLaunchKernelGGL((k_import_half<PP, true>), gr, bs, 0, s,
+                                                    (const double2 *)canon, f, p, geo));
+    }
 }
 
 void launch_export_half(FieldRef f, double *canon, int p, const Geom &geo, hipStream_t s) {

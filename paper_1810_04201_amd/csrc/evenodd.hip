@@ -5,6 +5,13 @@
 
 namespace wd {
 
+// canonical index of the first site (even x) of pair h
+__device__ __forceinline__ int pair_lex(const Geom &g, int h) {
+    int x, y, z, t;
+    coords_of(g, 2 * h, x, y, z, t);
+    return lex_of(g, x, y, z, t);
+}
+
 // Even-odd hopping term on half fields (one lane per site of one rhs):
 //   out_p = cs * c_p - k * H_{p,1-p} in_{1-p}
 // with H the hop sum of Eq. (1) (projectors exchanged for DAG).  Entry h of a
@@ -14,7 +21,10 @@ namespace wd {
 // summed in the order of the full stencil.
 // XR: the CG update r -= alpha out_p in place of storing out (the reduction
 // is then |r|^2; with HASC and RED).  LF: the link form.
-template <int PREC, bool DAG, bool RED, bool HASC, int GROUP, bool XR = false, int LF = PREC>
+// COUT: the output (p = 0) goes to a canonical float64 field (out.data, out.V
+// sites of the half) with zero at the odd sites.
+template <int PREC, bool DAG, bool RED, bool HASC, int GROUP, bool XR = false, int LF = PREC,
+          bool COUT = false>
 __global__ void __launch_bounds__(256) k_hop_half(Geom g, const void *__restrict__ gp,
                                                   const void *__restrict__ gq, int p, FieldRef in,
                                                   FieldRef c, FieldRef out, double k_d,
@@ -39,6 +49,11 @@ __global__ void __launch_bounds__(256) k_hop_half(Geom g, const void *__restrict
     }
     const FieldRef fin = rhs_view(in, rhs);
     const int h = sb * blockDim.x + threadIdx.x;
+    __shared__ __align__(16) char stage[COUT ? kSiteBlock / 64 * Spinor<PREC>::kTileBytes : 16];
+    const FieldRef tile = lds_view(
+        fin, stage + (COUT ? (threadIdx.x >> 6) * Spinor<PREC>::kTileBytes : 0));
+    int64_t pair = -1;
+    int second = 0;
     double nrm = 0.0;
     cx<R> o[12];
     if (h < out.V) {
@@ -86,8 +101,15 @@ __global__ void __launch_bounds__(256) k_hop_half(Geom g, const void *__restrict
             if (RED && !XR)
                 nrm += (double)o[k].re * (double)o[k].re + (double)o[k].im * (double)o[k].im;
         }
-        if constexpr (!XR) Spinor<PREC>::store(rhs_view(out, rhs), h, o);
+        if constexpr (COUT) {
+            pair = (int64_t)rhs * g.V + pair_lex(g, h);
+            second = i & 1;
+            Spinor<PREC>::store(tile, (int)(threadIdx.x & 63), o);
+        } else if constexpr (!XR) {
+            Spinor<PREC>::store(rhs_view(out, rhs), h, o);
+        }
     }
+    if constexpr (COUT) export_tile_pairs<PREC>((double2 *)out.data, pair, second, tile);
     if constexpr (XR) {
         R alpha;
         if (xr.alpha.nb) {
@@ -119,7 +141,9 @@ __global__ void __launch_bounds__(256) k_hop_half(Geom g, const void *__restrict
 // Hops are summed in the order of k_hop_half.  Forward links come from gp at
 // the output entry, backward ones from gq at the neighbour's entry.
 // RAG: parts as in k_dslash_tm where a half slice is no whole number of tiles.
-template <int PREC, bool DAG, bool RED, bool HASC, int GROUP, bool XR, int LF, bool RAG>
+// COUT: as in k_hop_half.
+template <int PREC, bool DAG, bool RED, bool HASC, int GROUP, bool XR, int LF, bool RAG,
+          bool COUT = false>
 __global__ void __launch_bounds__(kTmMaxBlock) k_hop_half_tm(Geom g, const void *__restrict__ gp,
                                                      const void *__restrict__ gq, int p,
                                                      FieldRef in, FieldRef c, FieldRef out,
@@ -284,7 +308,7 @@ __global__ void __launch_bounds__(kTmMaxBlock) k_hop_half_tm(Geom g, const void 
             nrm = xr_site_r<PREC>(xr, rhs, H, alpha, o, rpre, mine);
         else if constexpr (XR)
             nrm = xr_site<PREC>(xr, rhs, H, alpha, o, mine);
-        else
+        else if constexpr (!COUT)
             Spinor<PREC>::template store<WD_NT_OUT>(rhs_view(out, rhs), H, o);
         if (RED) {
             if (!mine) nrm = 0.0;
@@ -293,6 +317,15 @@ __global__ void __launch_bounds__(kTmMaxBlock) k_hop_half_tm(Geom g, const void 
             if ((tid & 63) == 0) wsum[odd][tid >> 6] = nrm;
         }
         __syncthreads();  // the current image is free for the next copy
+        if constexpr (COUT) {
+            FieldRef tile = cur;
+            tile.data = (char *)cur.data +
+                        __builtin_amdgcn_readfirstlane(tid >> 6) * Spinor<PREC>::kTileBytes;
+            Spinor<PREC>::store(tile, tid & 63, o);
+            export_tile_pairs<PREC>((double2 *)out.data,
+                                    mine ? (int64_t)rhs * g.V + pair_lex(g, H) : -1,
+                                    site_of_half(g, H, p) & 1, tile);
+        }
         if (RED && tid == 0) {
             double sum = 0.0;
             for (int v = 0; v < (int)(blockDim.x >> 6); ++v) sum += wsum[odd][v];
@@ -388,6 +421,59 @@ static void launch_hop_half_prec(const Geom &g, const void *gp, const void *gq, 
         case 6: launch_eo<PREC, true, true, false, false, LF>(g, gp, gq, p, in, c, out, k, cs, r, gate, nx, s); break;
         default: launch_eo<PREC, true, true, true, false, LF>(g, gp, gq, p, in, c, out, k, cs, r, gate, nx, s); break;
     }
+}
+
+// the even half of an operator's output, canonical, with zero odd sites
+template <int PREC, bool DAG, int LF>
+static void launch_eo_canon(const Geom &g, const void *gp, const void *gq, FieldRef in,
+                            FieldRef c, FieldRef out, double k, double cs, hipStream_t s) {
+    constexpr int G = HopGroup<PREC>::value;
+    const Gate none{nullptr, 0, GATE_ACTIVE};
+    const March m = eo_march<PREC>(g, in.nrhs, false, 0);
+    if constexpr (PREC != WD_F16) {
+        if (m.ok) {
+            auto go = [&](auto kern) {
+                allow_lds(kern, m.lds);
+                hipLaunchKernelGGL(kern, m.grid, m.bs, m.lds, s, g, gp, gq, 0, in, c, out, k, cs,
+                                   RedArgs{}, none, m.tch, m.ncols, m.p.w, XrArgs{});
+            };
+            if constexpr (PREC == WD_F64) {
+                if (m.p.ragged) {
+                    go(k_hop_half_tm<PREC, DAG, false, true, G, false, LF, true, true>);
+                    return;
+                }
+            }
+            go(k_hop_half_tm<PREC, DAG, false, true, G, false, LF, false, true>);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_hop_half<PREC, DAG, false, true, G, false, LF, true>),
+                       dim3(site_blocks(out.V) * in.nrhs), dim3(kSiteBlock), 0, s, g, gp, gq, 0,
+                       in, c, out, k, cs, RedArgs{}, none, XrArgs{});
+}
+
+void launch_hop_half_canon(const Geom &g, const void *gp, const void *gq, double k, double cs,
+                           int dagger, FieldRef in, FieldRef c, double *out, hipStream_t s,
+                           bool r12) {
+    FieldRef o = c;  // the half's sites
+    o.data = out;
+    auto go = [&](auto prec, auto lf) {
+        constexpr int P = decltype(prec)::value, F = decltype(lf)::value;
+        if (dagger)
+            launch_eo_canon<P, true, F>(g, gp, gq, in, c, o, k, cs, s);
+        else
+            launch_eo_canon<P, false, F>(g, gp, gq, in, c, o, k, cs, s);
+    };
+    if (in.prec == WD_F32)
+        go(Int<WD_F32>{}, Int<WD_F32>{});
+    else if (in.prec == WD_F16 && g.f16_links8)
+        go(Int<WD_F16>{}, Int<kLinkF16R8>{});
+    else if (in.prec == WD_F16)
+        go(Int<WD_F16>{}, Int<WD_F16>{});
+    else if (r12)
+        go(Int<WD_F64>{}, Int<kLinkF64R12>{});
+    else
+        go(Int<WD_F64>{}, Int<WD_F64>{});
 }
 
 template <int PREC, int LF = PREC>

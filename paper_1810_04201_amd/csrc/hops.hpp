@@ -160,4 +160,42 @@ __device__ __forceinline__ void export_tile(double2 *f, int64_t site, const Fiel
     wave_lds_sync();
 }
 
+// The same for 64 entries of an even half field: each result to its even site,
+// zero to the odd site beside it in x (the two are 384 consecutive bytes).  The
+// Schur operator is three launches with it instead of six: 30^3 x 60 float32 461
+// -> 345 us, 48^3 x 96 float64 4.58 -> 3.48 ms.
+// site: the canonical index of the pair's first site (even x) in f, -1 for none;
+// odd: 1 where the even-parity site is the second.  PREC float64 too.
+template <int PREC>
+__device__ __forceinline__ void export_tile_pairs(double2 *f, int64_t site, int odd,
+                                                  const FieldRef &tile) {
+    int lane = (int)(threadIdx.x & 63);
+    asm volatile("" : "+v"(lane));  // (see export_tile)
+    wave_lds_sync();
+    const int lo = (int)(uint32_t)site, hi = (int)(site >> 32);
+#pragma unroll
+    for (int j = 0; j < 24; ++j) {
+        const int e = j * 64 + lane, src = e / 24, k2 = e - src * 24;
+        const int second = k2 >= 12, k = second ? k2 - 12 : k2;
+        const int64_t st = ((int64_t)__shfl(hi, src, 64) << 32) | (uint32_t)__shfl(lo, src, 64);
+        const bool value = __shfl(odd, src, 64) == second;
+        d2_t o;
+        if constexpr (PREC == WD_F16) {
+            const float sc = *Spinor<WD_F16>::scale_ptr(tile, src);
+            const h2_t q = *(const h2_t *)(tile_elem(tile.data, Spinor<WD_F16>::kTileBytes, src,
+                                                     k >> 2) + (k & 3) * 4);
+            o = d2_t{(double)(sc * (float)q.x), (double)(sc * (float)q.y)};
+        } else if constexpr (PREC == WD_F32) {
+            const float *q = (const float *)(tile_elem(tile.data, Spinor<WD_F32>::kTileBytes, src,
+                                                       k >> 1) + (k & 1) * 8);
+            o = d2_t{(double)q[0], (double)q[1]};
+        } else {
+            o = *(const d2_t *)tile_elem(tile.data, Spinor<WD_F64>::kTileBytes, src, k);
+        }
+        if (!value) o = d2_t{0.0, 0.0};
+        if (st >= 0) *(d2_t *)((char *)f + st * kSiteBytes + k2 * 16) = o;
+    }
+    wave_lds_sync();
+}
+
 }  // namespace wd

@@ -233,6 +233,7 @@ static void timed(const char *name, hipStream_t s, F &&launch) {
     g_pending.push_back({name, a, b});
 }
 
+static const char *const kEoNames[3] = {"eo_f64", "eo_f32", "eo_f16"};
 static const char *const kDslashNames[3] = {"dslash_f64", "dslash_f32", "dslash_f16"};
 
 void dslash(wd_lattice *lat, const void *gauge, double kappa, int dagger, const FieldRef &in,
@@ -287,9 +288,8 @@ void hop_half(wd_lattice *lat, void *const gh[2], int p, double kappa, double cs
               Gate gate, hipStream_t s) {
     // D_{p,1-p} = hop_sign * kappa * H_{p,1-p}; the kernel computes cs c - k H in
     const double k = -lat->hop_sign * kappa;
-    static const char *names[3] = {"eo_f64", "eo_f32", "eo_f16"};
     const bool r12 = in.prec == WD_F64 && lat->eo64_r12 && gh[0] == lat->gauge_eo[WD_F64][0];
-    timed(names[in.prec], s, [&] {
+    timed(kEoNames[in.prec], s, [&] {
         launch_hop_half(lat->g, gh[p], gh[1 - p], p, k, cs, dagger, in, c, out, red, gate, s, r12);
     });
 }
@@ -587,25 +587,36 @@ int wd_apply_schur(wd_lattice *lat, double kappa, int prec, int dagger, int nrhs
     if (!gauge_eo_for(lat, prec, s, &err, gh)) return err;
     const int Vh = lat->g.V / 2;
     const size_t one = field_data_bytes(prec, Vh, nrhs) + 256;
+    // the second launch writes both halves of an output it can write in 16-byte
+    // elements
+    const bool direct = ((uintptr_t)out & 15) == 0;
     void *mem = nullptr;
-    hipError_t he = hipMallocAsync(&mem, 3 * one, s);
+    hipError_t he = hipMallocAsync(&mem, (direct ? 2 : 3) * one, s);
     if (he != hipSuccess)
-        return fail(WD_ERR_NOMEM, "workspace allocation of %zu bytes failed: %s", 3 * one,
-                    hipGetErrorString(he));
+        return fail(WD_ERR_NOMEM, "workspace allocation of %zu bytes failed: %s",
+                    (direct ? 2 : 3) * one, hipGetErrorString(he));
     char *cur = (char *)mem;
     FieldRef ve = carve(cur, prec, nrhs, Vh);
     cur = (char *)mem + one;
     FieldRef to = carve(cur, prec, nrhs, Vh);
-    cur = (char *)mem + 2 * one;
-    FieldRef oe = carve(cur, prec, nrhs, Vh);
     const Gate none{nullptr, 0, GATE_ACTIVE};
     launch_import_half(in, ve, 0, lat->g, s);
     // t_o = D_oe v_e ; out_e = v_e - D_eo t_o  (D^dag's blocks for dagger)
     hop_half(lat, gh, 1, kappa, 0.0, dagger, ve, FieldRef{}, to, nullptr, none, s);
-    hop_half(lat, gh, 0, -kappa, 1.0, dagger, to, ve, oe, nullptr, none, s);
-    launch_export_half(oe, out, 0, lat->g, s);
-    launch_zero(to, s);
-    launch_export_half(to, out, 1, lat->g, s);  // odd sites of out = 0
+    if (direct) {
+        const double k = lat->hop_sign * kappa;
+        const bool r12 = prec == WD_F64 && lat->eo64_r12;
+        timed(kEoNames[prec], s, [&] {
+            launch_hop_half_canon(lat->g, gh[0], gh[1], k, 1.0, dagger, to, ve, out, s, r12);
+        });
+    } else {
+        cur = (char *)mem + 2 * one;
+        FieldRef oe = carve(cur, prec, nrhs, Vh);
+        hop_half(lat, gh, 0, -kappa, 1.0, dagger, to, ve, oe, nullptr, none, s);
+        launch_export_half(oe, out, 0, lat->g, s);
+        launch_zero(to, s);
+        launch_export_half(to, out, 1, lat->g, s);  // odd sites of out = 0
+    }
     (void)hipFreeAsync(mem, s);
     WD_LAUNCH_CHECK();
     return WD_OK;

@@ -639,6 +639,11 @@ void launch_export_half(FieldRef f, double *canon, int p, const Geom &g, hipStre
 void launch_hop_half(const Geom &g, const void *gp, const void *gq, int p, double k,
                      double cs, int dagger, FieldRef in, FieldRef c, FieldRef out,
                      const RedArgs *red, Gate gate, hipStream_t s, bool r12 = false);
+// the same (p = 0, c present) with the even sites of a canonical float64 field
+// [rhs][V][24] as its output, the odd ones set to zero (out 16-byte aligned)
+void launch_hop_half_canon(const Geom &g, const void *gp, const void *gq, double k, double cs,
+                           int dagger, FieldRef in, FieldRef c, double *out, hipStream_t s,
+                           bool r12 = false);
 // the same with c present and its output q consumed where it is formed:
 // r -= alpha q (XrArgs on half fields), |r|^2 reduced with red.mode and
 // finalised; q is not stored

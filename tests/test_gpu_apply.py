@@ -116,3 +116,32 @@ def test_apply_tensors_off_16_bytes(env):
     ref = wilson.apply_D(U, src, dims, 0.12)
     assert site_rel_err(obuf[1:].cpu().numpy(), ref) < 1e-13
     lat.close()
+
+
+@pytest.mark.parametrize("dims,nrhs", [((8, 8, 8, 8), 1), ((4, 6, 8, 10), 3), ((2, 4, 2, 6), 2),
+                                       ((6, 10, 14, 4), 1), ((18, 6, 6, 10), 2)])
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16"])
+def test_schur_output_forms_agree(env, dims, nrhs, prec):
+    """The even-odd operator with its result written canonically by the second
+    launch (odd sites zero) and through separate exports (a buffer aligned to a
+    double only): the same bits; brick slices of whole tiles and not, one lane
+    per site and marching."""
+    torch, dev, wd = env
+    print(f"schur dims={dims} nrhs={nrhs} prec={prec}", flush=True)
+    V = int(np.prod(dims))
+    lat = wd.Lattice(dims)
+    lat.set_gauge(torch.from_numpy(gauge(dims, 35)).to(dev))
+    b = torch.from_numpy(synth.gaussian_sources(dims, [60 + k for k in range(nrhs)])).to(dev)
+    off = torch.zeros(b.numel() + 1, dtype=torch.float64, device=dev)
+    off[1:] = b.reshape(-1)
+    for dagger in (0, 1):
+        got = torch.full_like(b, float("nan"))
+        lat.apply_schur(0.12, b, got, prec=prec, dagger=dagger, nrhs=nrhs)
+        obuf = torch.full((b.numel() + 1,), float("nan"), dtype=torch.float64, device=dev)
+        lat.apply_schur(0.12, off[1:], obuf[1:], prec=prec, dagger=dagger, nrhs=nrhs)
+        torch.cuda.synchronize()
+        assert torch.equal(got.reshape(-1), obuf[1:])
+        par = np.indices(dims[::-1]).sum(axis=0).reshape(-1) % 2
+        out = got.cpu().numpy().reshape(nrhs, V, 24)
+        assert np.all(out[:, par == 1] == 0.0) and np.all(np.any(out[:, par == 0] != 0.0, axis=2))
+    lat.close()
