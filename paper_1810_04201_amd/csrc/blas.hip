@@ -5,7 +5,7 @@
 // reduction and p update), the float64 true residual, and norms.
 // All of them stream their operands once; the reductions are the
 // deterministic block reduction of device.hpp.
-#include "device.hpp"
+#include "hops.hpp"
 
 namespace wd {
 
@@ -209,98 +209,109 @@ __device__ __forceinline__ void store_from_double(const FieldRef &f, int i, cons
 // uniform over a workgroup.
 static dim3 field_grid(const FieldRef &f) { return dim3(site_blocks(f.V), f.nrhs); }
 
-// canonical [rhs][s][12][re,im] (lexicographic s) -> internal site i of rhs
-template <int PREC>
-__global__ void k_import(const double2 *__restrict__ canon, FieldRef f, Geom geo) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= geo.V) return;
-    const int r = blockIdx.y;
-    int x, y, z, t;
-    coords_of(geo, i, x, y, z, t);
-    const double2 *src = canon + ((size_t)r * geo.V + lex_of(geo, x, y, z, t)) * 12;
-    cx<double> v[12];
-#pragma unroll
-    for (int k = 0; k < 12; ++k) {
-        double2 d = src[k];
-        v[k] = {d.x, d.y};
-    }
-    store_from_double<PREC>(rhs_view(f, r), i, v);
-}
+// A field goes out through LDS, a wave's tile at a time (export_tile): a lane
+// writing its own site spreads every store over 64 places 192 bytes apart.
+// 48^3 x 96 out of float64 898 -> 781 us, out of float32 641 -> 587, binary16
+// 633 -> 494; two rhs of 18^3 x 36 in binary16 30 -> 17.
+// A half field comes in the same way, 12 lanes to a site (208 bytes apart there,
+// so that the lanes that then read a component of one site each meet different
+// banks): 30^3 x 60 into float32 90 -> 64 us.  A whole field's import reads per
+// lane: its 64 sites are rows of consecutive memory that the cache holds whole
+// until the lanes have read them (48^3 x 96 into float64 770 us, through LDS 779;
+// 24^3 x 48 x 12 into float32 421 and 428).
+constexpr int kImportWave = 64 * 208;
 
-template <int PREC>
-__global__ void k_export(FieldRef f, double2 *__restrict__ canon, Geom geo) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= geo.V) return;
-    const int r = blockIdx.y;
-    int x, y, z, t;
-    coords_of(geo, i, x, y, z, t);
-    cx<double> v[12];
-    load_as_double<PREC>(rhs_view(f, r), i, v);
-    double2 *dst = canon + ((size_t)r * geo.V + lex_of(geo, x, y, z, t)) * 12;
-#pragma unroll
-    for (int k = 0; k < 12; ++k) dst[k] = make_double2(v[k].re, v[k].im);
-}
-
-// canonical [rhs][s][12] <-> half field of parity p (entry h: site
-// site_of_half(h, p)); f.V = V / 2.  A wave's 64 sites come in through LDS, 12
-// lanes to a site (208 bytes apart there, so that the lanes that then read a
-// component of one site each meet different banks): a lane reading its own site
-// spreads every load over 64 places 384 bytes apart (30^3 x 60
-// into float32: 90 us, this way 64).  DIRECT does so:
-// buffers aligned to a double only.
-template <int PREC, bool DIRECT>
-__global__ void __launch_bounds__(kSiteBlock) k_import_half(const double2 *__restrict__ canon,
-                                                            FieldRef f, int p, Geom geo) {
+// src: the canonical field; lex: the lane's own site in it; img: the wave's
+// kImportWave bytes of LDS
+__device__ __forceinline__ void gather_site(const double2 *src, int64_t lex, char *img,
+                                            cx<double> v[12]) {
     typedef __attribute__((address_space(3))) void lds_void;
-    __shared__ __align__(16) char img[kSiteBlock / 64][DIRECT ? 16 : 64 * 208];
-    const int h = blockIdx.x * blockDim.x + threadIdx.x;
-    const bool mine = h < f.V;
-    const int r = blockIdx.y;
-    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    int x, y, z, t;
-    coords_of(geo, site_of_half(geo, mine ? h : f.V - 1, p), x, y, z, t);
-    const int lex = lex_of(geo, x, y, z, t);
-    const double2 *src = canon + (size_t)r * geo.V * 12;
-    cx<double> v[12];
-    if constexpr (DIRECT) {
-        if (!mine) return;
-        src += (size_t)lex * 12;
-#pragma unroll
-        for (int k = 0; k < 12; ++k) v[k] = {src[k].x, src[k].y};
-        store_from_double<PREC>(rhs_view(f, r), h, v);
-        return;
-    }
+    const int lane = threadIdx.x & 63;
+    const int lo = (int)(uint32_t)lex, hi = (int)(lex >> 32);
 #pragma unroll
     for (int j = 0; j < 13; ++j) {
         const int e = j * 64 + lane, site = e / 13, k = e - site * 13;
-        const size_t from = (size_t)__shfl(lex, site, 64) * 12 + (k < 12 ? k : 11);
-        __builtin_amdgcn_global_load_lds((const void *)(src + from),
-                                         (lds_void *)(img[w] + j * 1024), 16, 0, 0);
+        const int64_t st = ((int64_t)__shfl(hi, site, 64) << 32) | (uint32_t)__shfl(lo, site, 64);
+        __builtin_amdgcn_global_load_lds((const void *)(src + st * 12 + (k < 12 ? k : 11)),
+                                         (lds_void *)(img + j * 1024), 16, 0, 0);
     }
     __builtin_amdgcn_s_waitcnt(0);
     __builtin_amdgcn_wave_barrier();
     asm volatile("" ::: "memory");
-    if (!mine) return;
 #pragma unroll
     for (int k = 0; k < 12; ++k) {
-        const d2_t d = *(const d2_t *)(img[w] + lane * 208 + k * 16);
+        const d2_t d = *(const d2_t *)(img + lane * 208 + k * 16);
         v[k] = {d.x, d.y};
     }
-    store_from_double<PREC>(rhs_view(f, r), h, v);
 }
 
-template <int PREC>
-__global__ void k_export_half(FieldRef f, double2 *__restrict__ canon, int p, Geom geo) {
-    const int h = blockIdx.x * blockDim.x + threadIdx.x;
-    if (h >= f.V) return;
-    const int r = blockIdx.y;
+// canonical [rhs][s][12][re,im] (lexicographic s) <-> internal site i of rhs, or
+// (HALF) entry h of a half field of parity p: site site_of_half(h, p), f.V = V / 2.
+// DIRECT: each lane its own site, also where buffers are aligned to a double only.
+template <bool HALF>
+__device__ __forceinline__ int64_t canon_index(const Geom &geo, int r, int i, int p) {
     int x, y, z, t;
-    coords_of(geo, site_of_half(geo, h, p), x, y, z, t);
+    coords_of(geo, HALF ? site_of_half(geo, i, p) : i, x, y, z, t);
+    return (int64_t)r * geo.V + lex_of(geo, x, y, z, t);
+}
+
+template <int PREC, bool HALF, bool DIRECT>
+__global__ void __launch_bounds__(kSiteBlock) k_import(const double2 *__restrict__ canon,
+                                                       FieldRef f, int p, Geom geo) {
+    __shared__ __align__(16) char img[kSiteBlock / 64][DIRECT ? 16 : kImportWave];
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const bool mine = i < f.V;
+    const int r = blockIdx.y;
+    const int64_t lex = canon_index<HALF>(geo, r, mine ? i : f.V - 1, p);
     cx<double> v[12];
-    load_as_double<PREC>(rhs_view(f, r), h, v);
-    double2 *dst = canon + ((size_t)r * geo.V + lex_of(geo, x, y, z, t)) * 12;
+    if constexpr (DIRECT) {
 #pragma unroll
-    for (int k = 0; k < 12; ++k) dst[k] = make_double2(v[k].re, v[k].im);
+        for (int k = 0; k < 12; ++k) v[k] = {canon[lex * 12 + k].x, canon[lex * 12 + k].y};
+    } else {
+        gather_site(canon, lex, img[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)], v);
+    }
+    if (mine) store_from_double<PREC>(rhs_view(f, r), i, v);
+}
+
+template <int PREC, bool HALF, bool DIRECT>
+__global__ void __launch_bounds__(kSiteBlock) k_export(FieldRef f, double2 *__restrict__ canon,
+                                                       int p, Geom geo) {
+    typedef __attribute__((address_space(3))) void lds_void;
+    constexpr int TB = (int)Spinor<PREC>::kTileBytes;
+    __shared__ __align__(16) char img[kSiteBlock / 64][DIRECT ? 16 : TB];
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const bool mine = i < f.V;
+    const int r = blockIdx.y;
+    const FieldRef fr = rhs_view(f, r);
+    if constexpr (DIRECT) {
+        if (!mine) return;
+        const int64_t lex = canon_index<HALF>(geo, r, i, p);
+        cx<double> v[12];
+        load_as_double<PREC>(fr, i, v);
+#pragma unroll
+        for (int k = 0; k < 12; ++k) canon[lex * 12 + k] = make_double2(v[k].re, v[k].im);
+    } else {
+        // whole tiles: the last one of a field is padded in memory
+        const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const int first = __builtin_amdgcn_readfirstlane(i & ~63);
+        if (first >= f.V) return;
+        const int64_t lex = mine ? canon_index<HALF>(geo, r, i, p) : -1;
+        const char *src = (const char *)fr.data + (size_t)(first >> 6) * TB;
+        const int lane = threadIdx.x & 63;
+#pragma unroll
+        for (int k = 0; k < TB / 1024; ++k)
+            __builtin_amdgcn_global_load_lds((const void *)(src + k * 1024 + lane * 16),
+                                             (lds_void *)(img[w] + k * 1024), 16, 0, 0);
+        if constexpr (PREC == WD_F16)
+            __builtin_amdgcn_global_load_lds((const void *)(src + 3072 + lane * 4),
+                                             (lds_void *)(img[w] + 3072), 4, 0, 0);
+        __builtin_amdgcn_s_waitcnt(0);
+        __builtin_amdgcn_wave_barrier();
+        asm volatile("" ::: "memory");
+        FieldRef tile = fr;
+        tile.data = img[w];
+        export_tile<PREC>(canon, lex, tile);
+    }
 }
 
 template <int PREC>
@@ -357,30 +368,45 @@ __global__ void __launch_bounds__(kSiteBlock) k_accum_zero(FieldRef x, FieldRef 
         default: { constexpr int PP = WD_F16; __VA_ARGS__; } break;     \
     }
 
-void launch_import(const double *canon, FieldRef f, const Geom &geo, hipStream_t s) {
-    WD_DISPATCH_PREC(f.prec, hipLaunchKernelGGL(k_import<PP>, field_grid(f), dim3(kSiteBlock), 0,
-                                                s, (const double2 *)canon, f, geo));
-}
-
-void launch_export(FieldRef f, double *canon, const Geom &geo, hipStream_t s) {
-    WD_DISPATCH_PREC(f.prec, hipLaunchKernelGGL(k_export<PP>, field_grid(f), dim3(kSiteBlock), 0,
-                                                s, f, (double2 *)canon, geo));
-}
-
-void launch_import_half(const double *canon, FieldRef f, int p, const Geom &geo, hipStream_t s) {
+template <bool HALF>
+static void import_any(const double *canon, FieldRef f, int p, const Geom &geo, hipStream_t s) {
     const dim3 gr = field_grid(f), bs(kSiteBlock);
+    const double2 *c = (const double2 *)canon;
+    if constexpr (HALF) {
+        if (((uintptr_t)canon & 15) == 0) {
+            WD_DISPATCH_PREC(f.prec, hipLaunchKernelGGL((k_import<PP, HALF, false>), gr, bs, 0, s,
+                                                        c, f, p, geo));
+            return;
+        }
+    }
+    WD_DISPATCH_PREC(f.prec, hipLaunchKernelGGL((k_import<PP, HALF, true>), gr, bs, 0, s, c, f, p,
+                                                geo));
+}
+
+template <bool HALF>
+static void export_any(FieldRef f, double *canon, int p, const Geom &geo, hipStream_t s) {
+    const dim3 gr = field_grid(f), bs(kSiteBlock);
+    double2 *c = (double2 *)canon;
     if (((uintptr_t)canon & 15) == 0) {
-        WD_DISPATCH_PREC(f.prec, hipLaunchKernelGGL((k_import_half<PP, false>), gr, bs, 0, s,
-                                                    (const double2 *)canon, f, p, geo));
+        WD_DISPATCH_PREC(f.prec, hipLaunchKernelGGL((k_export<PP, HALF, false>), gr, bs, 0, s, f,
+                                                    c, p, geo));
     } else {
-        WD_DISPATCH_PREC(f.prec, hipLaunchKernelGGL((k_import_half<PP, true>), gr, bs, 0, s,
-                                                    (const double2 *)canon, f, p, geo));
+        WD_DISPATCH_PREC(f.prec, hipLaunchKernelGGL((k_export<PP, HALF, true>), gr, bs, 0, s, f, c,
+                                                    p, geo));
     }
 }
 
+void launch_import(const double *canon, FieldRef f, const Geom &geo, hipStream_t s) {
+    import_any<false>(canon, f, 0, geo, s);
+}
+void launch_export(FieldRef f, double *canon, const Geom &geo, hipStream_t s) {
+    export_any<false>(f, canon, 0, geo, s);
+}
+void launch_import_half(const double *canon, FieldRef f, int p, const Geom &geo, hipStream_t s) {
+    import_any<true>(canon, f, p, geo, s);
+}
 void launch_export_half(FieldRef f, double *canon, int p, const Geom &geo, hipStream_t s) {
-    WD_DISPATCH_PREC(f.prec, hipLaunchKernelGGL(k_export_half<PP>, field_grid(f), dim3(kSiteBlock),
-                                                0, s, f, (double2 *)canon, p, geo));
+    export_any<true>(f, canon, p, geo, s);
 }
 
 void launch_zero(FieldRef f, hipStream_t s) {

@@ -150,10 +150,12 @@ __device__ __forceinline__ void export_tile(double2 *f, int64_t site, const Fiel
             const h2_t q = *(const h2_t *)(tile_elem(tile.data, Spinor<WD_F16>::kTileBytes, src,
                                                      k >> 2) + (k & 3) * 4);
             o = d2_t{(double)(sc * (float)q.x), (double)(sc * (float)q.y)};
-        } else {
+        } else if constexpr (PREC == WD_F32) {
             const float *q = (const float *)(tile_elem(tile.data, Spinor<WD_F32>::kTileBytes, src,
                                                        k >> 1) + (k & 1) * 8);
             o = d2_t{(double)q[0], (double)q[1]};
+        } else {
+            o = *(const d2_t *)tile_elem(tile.data, Spinor<WD_F64>::kTileBytes, src, k);
         }
         if (st >= 0) *(d2_t *)((char *)f + st * kSiteBytes + k * 16) = o;
     }

@@ -145,3 +145,34 @@ def test_schur_output_forms_agree(env, dims, nrhs, prec):
         out = got.cpu().numpy().reshape(nrhs, V, 24)
         assert np.all(out[:, par == 1] == 0.0) and np.all(np.any(out[:, par == 0] != 0.0, axis=2))
     lat.close()
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16"])
+@pytest.mark.parametrize("dims,nrhs", [((2, 2, 2, 2), 1), ((4, 4, 4, 4), 5), ((6, 2, 2, 4), 3),
+                                       ((14, 10, 6, 8), 2)])
+def test_export_forms_agree(env, dims, nrhs, prec):
+    """A field's export through LDS (fields of part of a tile, of whole ones, of
+    ragged ones) writes what the per-lane one writes to a buffer aligned to a
+    double only, and nothing around it; the conversions there and back are exact in
+    float64 and one rounding in float32."""
+    torch, dev, wd = env
+    print(f"export dims={dims} nrhs={nrhs} prec={prec}", flush=True)
+    lat = wd.Lattice(dims)
+    n = nrhs * int(np.prod(dims)) * 24
+    src = torch.from_numpy(np.random.default_rng(11).standard_normal(n)).to(dev)
+    f = wd.Field(lat, prec, nrhs)
+    f.load(src)
+    even = torch.full((n + 64,), -7.0, dtype=torch.float64, device=dev)
+    odd = torch.full((n + 64,), -7.0, dtype=torch.float64, device=dev)
+    f.store(even[32:32 + n])
+    f.store(odd[33:33 + n])
+    torch.cuda.synchronize()
+    assert torch.equal(even[32:32 + n], odd[33:33 + n])
+    for buf, k in ((even, 32), (odd, 33)):
+        assert bool((buf[:k] == -7.0).all()) and bool((buf[k + n:] == -7.0).all())
+    if prec == "f64":
+        assert torch.equal(even[32:32 + n], src)
+    elif prec == "f32":
+        assert torch.equal(even[32:32 + n], src.float().double())
+    f.close()
+    lat.close()
