@@ -136,7 +136,7 @@ __global__ void __launch_bounds__(kApplySiteBlock, 1)
 // 16 lanes reading one component of consecutive sites meet 16 different
 // bank groups).  A tile of 64 sites is 13 KiB.
 constexpr int kImgSite = 208;
-constexpr int kImgTile = 64 * kImgSite;
+static_assert(kImgTile == 64 * kImgSite, "image tile");
 
 typedef __attribute__((address_space(3))) void lds_void;
 
@@ -330,7 +330,7 @@ static void launch_march(const Geom &g, const void *gauge, double kappa, int dag
     const ApplyShape a = apply_shape(g, nrhs);
     const int threads = (a.w + 63) / 64 * 64;
     const dim3 grid(a.ncols * a.nchunks * a.nsub * nrhs), bs(threads);
-    const size_t lds = 2 * (size_t)(threads / 64) * kImgTile;
+    const size_t lds = apply_lds(threads);
     auto go = [&](auto k) {
         (void)hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize,
                                   (int)lds);

@@ -20,6 +20,10 @@ inline bool apply_march(const Geom &g, int nrhs) {
     return g.bvol >= 32 && (int64_t)g.V * nrhs >= 65536;
 }
 
+// a workgroup's two slice images: tiles of 64 sites, 208 bytes apart
+constexpr int kImgTile = 64 * 208;
+inline size_t apply_lds(int threads) { return 2 * (size_t)(threads / 64) * kImgTile; }
+
 // launch shape of the marching form
 struct ApplyShape {
     int w, nsub;  // sites per part of a brick slice, parts
@@ -37,6 +41,12 @@ inline ApplyShape apply_shape(const Geom &g, int nrhs) {
         return e ? atoi(e) : 0;
     }();
     a.tchunk = tm_chunk_len(g, nrhs * a.nsub, env);
+    if (env <= 0) {
+        const int threads = (a.w + 63) / 64 * 64;
+        a.tchunk = balanced_chunk(Lt, (int64_t)a.ncols * a.nsub * nrhs,
+                                  wgs_at_once(WD_F64, threads, apply_lds(threads)), a.tchunk,
+                                  chunk_gain(WD_F64, nrhs));
+    }
     a.nchunks = (Lt + a.tchunk - 1) / a.tchunk;
     return a;
 }

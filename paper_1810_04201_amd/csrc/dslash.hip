@@ -670,8 +670,15 @@ template <int LF>
 static void launch_halo_lf(const Geom &g, const void *gauge, double kappa, int dagger,
                            FieldRef in, FieldRef out, const Halo &region, hipStream_t s) {
     const PartShape p = tm_part(g, WD_F64);
-    const int tch = tm_chunk(g, in.nrhs * p.nsub);
     const int ncols = g.V / (g.L[3] * g.bvol);
+    const size_t lds = 2 * slice_bytes<WD_F64>(p.threads);
+    int tch = tm_chunk(g, in.nrhs * p.nsub);
+    // (a slab in two launches keeps short chunks: the longer the ends' chunks,
+    // the less is left to run while the faces travel)
+    if (region.region == 0 && env_chunk() <= 0)
+        tch = balanced_chunk(g.L[3], (int64_t)ncols * p.nsub * in.nrhs,
+                             wgs_at_once(WD_F64, p.threads, lds), tch,
+                             chunk_gain(WD_F64, in.nrhs));
     // chunks of this launch: all; the interior ones (neither slice 0 nor
     // Lt - 1: no staged face is read); or the one or two holding the ends
     const int nch = (g.L[3] + tch - 1) / tch;
@@ -688,7 +695,6 @@ static void launch_halo_lf(const Geom &g, const void *gauge, double kappa, int d
     }
     if (count <= 0) return;
     const dim3 grid(ncols * count * p.nsub * in.nrhs), bs(p.threads);
-    const size_t lds = 2 * slice_bytes<WD_F64>(p.threads);
     constexpr int G = HopGroup<WD_F64>::value;
     const Gate none{nullptr, 0, GATE_ACTIVE};
     auto go = [&](auto k) {

@@ -256,13 +256,14 @@ __device__ __forceinline__ double xr_site(const XrArgs &a, int rhs, int i,
 }
 
 // WD_TCHUNK overrides the marching stencil's chunk length (tuning)
-static int tm_chunk(const Geom &g, int nrhs) {
+static int env_chunk() {
     static const int env = [] {
         const char *e = getenv("WD_TCHUNK");
         return e ? atoi(e) : 0;
     }();
-    return tm_chunk_len(g, nrhs, env);
+    return env;
 }
+static int tm_chunk(const Geom &g, int nrhs) { return tm_chunk_len(g, nrhs, env_chunk()); }
 
 // WD_SITE_KERNEL=1 forces the one-lane-per-site stencil everywhere (tuning)
 static const bool g_force_site_kernel = [] {
@@ -320,6 +321,12 @@ static March march_of(const Geom &g, int n, int nrhs) {
     const int parts = m.ncols * m.p.nsub * nrhs;
     if (m.tch == 1 && parts * g.L[3] > at_once && parts * ((g.L[3] + 1) / 2) <= at_once)
         m.tch = 2;
+    // (not in binary16, whose steps are too short for the count: 24^3 x 48 38 us
+    // at one and two slices, 40 at three, which it ranks first; nor from one
+    // slice in float32, the same: 18^3 x 36 x 2 38 us, 40 at three)
+    if ((PREC == WD_F64 || (PREC == WD_F32 && m.tch > 1)) && env_chunk() <= 0)
+        m.tch = balanced_chunk(g.L[3], parts, wgs_at_once(PREC, m.p.threads, m.lds), m.tch,
+                               chunk_gain(PREC, nrhs));
     m.chunks = (g.L[3] + m.tch - 1) / m.tch;
     m.grid = dim3(m.ncols * m.chunks * m.p.nsub * nrhs);
     m.bs = dim3(m.p.threads);

@@ -468,6 +468,53 @@ inline int tm_chunk_len(const Geom &g, int nrhs, int env_chunk) {
     return (Lt + nch - 1) / nch;
 }
 
+// Workgroups of threads lanes and lds bytes that the chip holds at once: 256
+// CUs of 160 KiB and, with the marching kernels' registers, 8 waves in float64,
+// 16 in the others.
+inline int wgs_at_once(int prec, int threads, size_t lds) {
+    const int by_waves = (prec == WD_F64 ? 8 : 16) / (threads / 64);
+    const int by_lds = (int)(163840 / lds);
+    const int n = by_waves < by_lds ? by_waves : by_lds;
+    return 256 * (n > 0 ? n : 1);
+}
+
+// The least gain by that count for which the length is changed, both sides of
+// the line in us: one rhs in float64, D on canonical spinors at 32^3 x 64 (5% by
+// the count) 406 -> 362, the stencil at 30^3 x 60 (7%) 321 -> 319; in float32
+// 24^3 x 48 (10%) 59 -> 56.  Several rhs, which share their links through L2,
+// gain less: 16^3 x 32 x 12 float32 (15%) 102 -> 95, but 24^3 x 48 x 2 float64 (9%)
+// 211 -> 215, 32^3 x 64 x 4 float32 (5%) 582 -> 590.
+inline double chunk_gain(int prec, int nrhs) {
+    return nrhs > 1 ? 1.0 / 8 : prec == WD_F64 ? 1.0 / 32 : 1.0 / 16;
+}
+
+// Chunk length of a marching launch of `parts` workgroups per chunk, `at_once`
+// of them on the chip at a time, with c0 to start from.  A launch takes its
+// rounds of workgroups, each as long as its slices and half of one more (a
+// chunk reads a slice before its first and one after its last), and a last
+// round that fills the chip to f still 0.35 + 0.65 f of one.  That fits the
+// times of all lengths from 2 to 24 within 10% (32^3 x 64 float64, 128 parts,
+// 256 at once: 409 us at 4, 418 at 6, 385 at 8, 426 at 10, 386 at 16, 486 at 24;
+// 24^3 x 48, 72 parts, 512 at once: 121 us at 2, 134 at 6, 108 at 7, 151 at 12).
+// The length of the least count where that is more than `gain` below c0's;
+// smaller differences are within the fit (chunk_gain).  c0 against the chosen
+// length: stencil 32^3 x 64 float64 410 -> 377 us, 40^3 x 80 1002 -> 925, float32
+// 479 -> 449, 36^3 x 72 328 -> 298; CG iteration 24^3 x 48 float64 408 -> 388,
+// float32 194 -> 190, 32^3 x 64 float32 588 -> 567; even-odd operator 24^3 x 48
+// float64 254 -> 228; D on canonical spinors 16^3 x 32 30.6 -> 26.7, 24^3 x 48
+// 130 -> 117.
+inline int balanced_chunk(int Lt, int64_t parts, int at_once, int c0, double gain) {
+    auto cost = [&](int c) {
+        const int64_t wgs = parts * ((Lt + c - 1) / c), full = wgs / at_once;
+        const double last = (double)(wgs - full * at_once) / at_once;
+        return ((double)full + (last > 0 ? 0.35 + 0.65 * last : 0.0)) * (c + 0.5);
+    };
+    int best = c0;
+    for (int c = 1; c <= Lt; ++c)
+        if (cost(c) < cost(best)) best = c;
+    return cost(best) < (1.0 - gain) * cost(c0) ? best : c0;
+}
+
 // column chunks of the time-marching stencil (each runs bvol / w
 // workgroups per rhs)
 inline int tm_blocks(const Geom &g, int chunk_len) {

@@ -52,6 +52,20 @@ int main() {
                     ++fails;
             }
     }
+    // chunk lengths: in range; c0 itself where one round holds everything; never
+    // one that the count behind the choice ranks behind c0 (whole rounds only)
+    for (int Lt = 2; Lt <= 96; Lt += 2)
+        for (long long parts = 1; parts <= 6000; parts = parts * 3 / 2 + 1)
+            for (int at : {256, 512, 768, 1024, 1536})
+                for (int c0 : {1, 2, 5, Lt}) {
+                    if (c0 > Lt) continue;
+                    const int c = wd::balanced_chunk(Lt, parts, at, c0, 1.0 / 32);
+                    if (c < 1 || c > Lt) ++fails;
+                    if (wd::balanced_chunk(Lt, parts, at, c0, 1.0) != c0) ++fails;
+                    const long long r0 = (parts * ((Lt + c0 - 1) / c0) + at - 1) / at;
+                    const long long r = (parts * ((Lt + c - 1) / c) + at - 1) / at;
+                    if (c > c0 && r >= r0) ++fails;
+                }
     printf(fails ? "FAIL %d\n" : "OK\n", fails);
     return fails ? 1 : 0;
 }
