@@ -169,8 +169,8 @@ int wd_apply(wd_lattice *lat, double kappa, int prec, int dagger, int nrhs, cons
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): wd_apply
- * with no allocation.  The two internal-layout fields wd_apply allocates
- * live instead in a fixed 128 MiB scratch array that the library holds on
+ * with no allocation.  The internal-layout fields (up to two) that wd_apply
+ * allocates where it needs them live instead in a fixed 128 MiB scratch array that the library holds on
  * each GPU it runs on until the process ends; the call makes no hipMalloc,
  * hipFree or allocating library call.  2 * (internal field bytes of nrhs
  * spinors on V sites) must fit the scratch (e.g. float64 with V * nrhs up to

@@ -345,6 +345,9 @@ static void launch_march(const Geom &g, const void *gauge, double kappa, int dag
 
 bool apply_direct_ok(const Geom &g, int prec, int nrhs, const double *in, const double *out) {
     if ((((uintptr_t)in | (uintptr_t)out) & 15) != 0) return false;
+    // fields that share memory: through an import, which reads all of `in` first
+    const size_t n = (size_t)g.V * nrhs * 24;
+    if ((uintptr_t)in < (uintptr_t)(out + n) && (uintptr_t)out < (uintptr_t)(in + n)) return false;
     return prec == WD_F64 || (prec == WD_F32 && !apply_march(g, nrhs));
 }
 

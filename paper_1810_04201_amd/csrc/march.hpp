@@ -163,10 +163,11 @@ __device__ __forceinline__ void pin(cx<R> v[12]) {
 // Wait until this wave's outstanding copies have landed in LDS.  Only this
 // wave reads its tiles before the barrier that ends the step, so no barrier is
 // needed here: with one, the waves of a workgroup met twice per slice and
-// idled together (r-updating float64 iteration at 48^3 x 96 6.03 -> 5.76 ms
-// without it, float32 stencil 0.93 -> 0.88 ms).  Binary16 keeps the barrier:
-// its plain stencil measured equal without it (0.55 ms), its r-updating
-// iteration slower (1.97 -> 2.15 ms).
+// idled together (both forms timed in turn: the 12-source float32 solve on
+// 24^3 x 48 1.023 times as fast, a 48^3 x 12 slab pass 1.019; single launches at
+// 48^3 x 96 differ by less than their runs do).  Binary16 keeps the barrier: its plain stencil
+// measured equal without it (0.55 ms), its r-updating iteration slower (1.97 ->
+// 2.15 ms).
 template <int PREC>
 __device__ __forceinline__ void copy_landed() {
     __builtin_amdgcn_s_waitcnt(0);
