@@ -63,7 +63,7 @@ SPINOR_BYTES = {"f64": 192, "f32": 96, "f16": 52}
 HBM_PEAK_GBS = 8000.0
 METRIC = "dslash GFLOP/s & HBM GB/s; CG time-to-1e-10 residual, mixed vs FP64"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "dslash_traffic_48x48x48x96.json")
-KERNEL_SOURCES = ["dslash.hip", "device.hpp", "wd_internal.hpp"]
+KERNEL_SOURCES = ["dslash.hip", "march.hpp", "hops.hpp", "device.hpp", "wd_internal.hpp"]
 
 
 def log(*a):
@@ -1050,8 +1050,9 @@ def multi_summary(args):
                          f"{(fb + wb) / ns / 1e3:.2f} |")
         # one inner CG iteration: the reducing stencil (q = D p), the
         # r-updating one and the x/p update
-        pats = (r"k_dslash_tm<1, false, true, \d+, false, false, 1>",
-                r"k_dslash_tm<1, true, true, \d+, false, true, 1>", r"k_update_xp<1, 1>")
+        pats = (r"k_dslash_tm<1, false, true, \d+, false, false, 1(, false, (true|false))?>",
+                r"k_dslash_tm<1, true, true, \d+, false, true, 1(, false, (true|false))?>",
+                r"k_update_xp<1, 1(, (true|false))?>")
         it = [r for r in rows if any(re.fullmatch(p, r[0]) for p in pats)]
         if len(it) == 3:
             ns = sum(r[2] for r in it)
@@ -1102,7 +1103,8 @@ def pmc_summary(args):
     # kernel names carry the hop scheduling group (a tuning constant) in the
     # fourth template argument: match any
     def named(rows, i, dag, red, xr, lf):
-        pat = re.compile(rf"k_dslash_tm<{i}, {dag}, {red}, \d+, false, {xr}, {lf}>")
+        pat = re.compile(rf"k_dslash_tm<{i}, {dag}, {red}, \d+, false, {xr}, {lf}"
+                         r"(, false, (true|false))?>")
         return [r for r in rows if pat.search(r["name"])]
 
     kinds = []
@@ -1154,14 +1156,15 @@ def pmc_summary(args):
             "algorithmic_bytes_per_rhs_site": 208,
             "fetch_bytes_per_rhs_site": round(fk * 1024 * ff / n, 1),
             "write_bytes_per_rhs_site": round(wk * 1024 * wf / n, 1)}
-    # even-odd half-field stencil (k_hop_half): a launch writes V/2 sites,
-    # reads every link once and the other half's spinors, and (every second
-    # launch of M) a c field
+    # even-odd half-field stencil, M's first launch (t_o = D_oe v_e; the second
+    # one also writes the canonical result): writes V/2 sites, reads every link
+    # once and the other half's spinors
     for prec, i in (("f64", 0), ("f16", 2)):
         # the marching form where the probe ran it, else one lane per site
         for tag in (f"k_hop_half_tm<{i}", f"k_hop_half<{i}"):
-            fr = [r for r in fetch if tag in r["name"]]
-            wr = [r for r in write if tag in r["name"]]
+            pat = re.compile(re.escape(tag) + r", \w+, \w+, false, \d+, \w+, (\d)")
+            fr = [r for r in fetch if pat.search(r["name"])]
+            wr = [r for r in write if pat.search(r["name"])]
             if fr and wr:
                 break
         if not fr or not wr:
@@ -1169,10 +1172,10 @@ def pmc_summary(args):
         fk = statistics.mean(r["FETCH_SIZE"] for r in fr)
         wk = statistics.mean(r["WRITE_SIZE"] for r in wr)
         traffic = fk * 1024 * ff + wk * 1024 * wf
-        # the last template argument is the link form (3: float64, 12 reals)
-        link = 384 if prec == "f64" and fr[0]["name"].split(">")[0].endswith(", 3") else \
+        # the link form (3: float64, 12 reals)
+        link = 384 if prec == "f64" and pat.search(fr[0]["name"]).group(1) == "3" else \
             LINK_BYTES[prec]
-        per_site = 2 * link + 2.5 * SPINOR_BYTES[prec]
+        per_site = 2 * link + 2 * SPINOR_BYTES[prec]
         alg = V // 2 * per_site
         out["kernels"][f"hop_half_{prec}"] = {
             "kernel": tag.split("<")[0],
