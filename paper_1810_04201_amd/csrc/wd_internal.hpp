@@ -478,8 +478,8 @@ inline int wgs_at_once(int prec, int threads, size_t lds) {
     return 256 * (n > 0 ? n : 1);
 }
 
-// The least gain by that count for which the length is changed, both sides of
-// the line in us: one rhs in float64, D on canonical spinors at 32^3 x 64 (5% by
+// The least gain by balanced_chunk's count for which it changes the length, both
+// sides of the line in us: one rhs in float64, D on canonical spinors at 32^3 x 64 (5% by
 // the count) 406 -> 362, the stencil at 30^3 x 60 (7%) 321 -> 319; in float32
 // 24^3 x 48 (10%) 59 -> 56.  Several rhs, which share their links through L2,
 // gain less: 16^3 x 32 x 12 float32 (15%) 102 -> 95, but 24^3 x 48 x 2 float64 (9%)
@@ -493,9 +493,10 @@ inline double chunk_gain(int prec, int nrhs) {
 // rounds of workgroups, each as long as its slices and half of one more (a
 // chunk reads a slice before its first and one after its last), and a last
 // round that fills the chip to f still 0.35 + 0.65 f of one.  That fits the
-// times of all lengths from 2 to 24 within 10% (32^3 x 64 float64, 128 parts,
-// 256 at once: 409 us at 4, 418 at 6, 385 at 8, 426 at 10, 386 at 16, 486 at 24;
-// 24^3 x 48, 72 parts, 512 at once: 121 us at 2, 134 at 6, 108 at 7, 151 at 12).
+// times at 32^3 x 64 float64 (128 parts, 256 at once) within 5% from 2 to 24
+// slices (409 us at 4, 418 at 6, 385 at 8, 426 at 10, 386 at 16, 486 at 24), and
+// at 24^3 x 48 (72 parts, 512 at once) within 11% to 10 slices, 17% low at 12
+// (121 us at 2, 134 at 6, 108 at 7, 132 at 10, 151 at 12).
 // The length of the least count where that is more than `gain` below c0's;
 // smaller differences are within the fit (chunk_gain).  c0 against the chosen
 // length: stencil 32^3 x 64 float64 410 -> 377 us, 40^3 x 80 1002 -> 925, float32
@@ -510,9 +511,17 @@ inline int balanced_chunk(int Lt, int64_t parts, int at_once, int c0, double gai
         return ((double)full + (last > 0 ? 0.35 + 0.65 * last : 0.0)) * (c + 0.5);
     };
     int best = c0;
-    for (int c = 1; c <= Lt; ++c)
-        if (cost(c) < cost(best)) best = c;
-    return cost(best) < (1.0 - gain) * cost(c0) ? best : c0;
+    const double start = cost(c0);
+    double least = start;
+    // of the lengths that give n chunks the shortest costs least
+    for (int c = 1;;) {
+        const double v = cost(c);
+        if (v < least) best = c, least = v;
+        const int n = (Lt + c - 1) / c;
+        if (n == 1) break;
+        c = (Lt + n - 2) / (n - 1);
+    }
+    return least < (1.0 - gain) * start ? best : c0;
 }
 
 // column chunks of the time-marching stencil (each runs bvol / w

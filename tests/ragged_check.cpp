@@ -62,6 +62,17 @@ int main() {
                     const int c = wd::balanced_chunk(Lt, parts, at, c0, 1.0 / 32);
                     if (c < 1 || c > Lt) ++fails;
                     if (wd::balanced_chunk(Lt, parts, at, c0, 1.0) != c0) ++fails;
+                    // the least count over all lengths
+                    int best = c0;
+                    auto cost = [&](int k) {
+                        const long long wgs = parts * ((Lt + k - 1) / k);
+                        const double last = (double)(wgs % at) / at;
+                        return ((double)(wgs / at) + (last > 0 ? 0.35 + 0.65 * last : 0.0)) *
+                               (k + 0.5);
+                    };
+                    for (int k = 1; k <= Lt; ++k)
+                        if (cost(k) < cost(best)) best = k;
+                    if (c != (cost(best) < (1.0 - 1.0 / 32) * cost(c0) ? best : c0)) ++fails;
                     const long long r0 = (parts * ((Lt + c0 - 1) / c0) + at - 1) / at;
                     const long long r = (parts * ((Lt + c - 1) / c) + at - 1) / at;
                     if (c > c0 && r >= r0) ++fails;
