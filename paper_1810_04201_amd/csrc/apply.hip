@@ -167,7 +167,8 @@ __global__ void __launch_bounds__(kApplyPart, 2)
     const int Lt = g.L[3], bvol = g.bvol, V3 = g.V / Lt;
     const int n = bvol - h * w < w ? bvol - h * w : w;  // sites of this part
     const int tid = (int)threadIdx.x, lane = tid & 63;
-    int l = tid < n ? tid : n - 1;
+    const PartLane pl = part_lane(tid, n);
+    int l = pl.l;
     ColSite s = col_site(g, col, h * w + l);
     const int t0 = chunk * tchunk;
     const int t1 = t0 + tchunk < Lt ? t0 + tchunk : Lt;
@@ -278,14 +279,14 @@ __global__ void __launch_bounds__(kApplyPart, 2)
         fence();
         cx<R> ut[9];
         Link<LF>::template load<true>(gauge, 3, i, ut);
-        // this wave's copy of the next slice has landed: only this wave reads
-        // its tile before the barrier that ends the step
+        // this wave's copy of the next slice has landed: until the barrier that
+        // ends the step a lane reads its own place of it
         __builtin_amdgcn_s_waitcnt(0);
         __builtin_amdgcn_wave_barrier();
         asm volatile("" ::: "memory");
         {
             cx<R> nx[12];
-            load12<R>(nxt + l * kImgSite, nx);
+            load12<R>(nxt + pl.place * kImgSite, nx);
             hop_p<3, SF, false>(nx, ut, g.antiperiodic && t == Lt - 1, acc);
         }
         accumulate<3, SB>(cw0, cw1, acc);

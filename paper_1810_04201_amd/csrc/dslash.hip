@@ -173,10 +173,12 @@ __global__ void __launch_bounds__(kTmMaxBlock) k_dslash_tm(Geom g, const void *_
     const int chunk = HALO ? halo.cfirst + lchunk * halo.cstep : lchunk;
     const int Lt = g.L[3], bvol = g.bvol;
     const int tid = (int)threadIdx.x;
-    // sites of this workgroup's part of a slice; lanes past it repeat its last
+    // sites of this workgroup's part of a slice; lanes past it repeat its last,
+    // with its result (what is not a plain store of it asks `mine`)
     const int wvol = RAG && bvol - h * w < w ? bvol - h * w : w;
     const bool mine = !RAG || tid < wvol;
-    const int l = mine ? tid : wvol - 1;
+    const PartLane pl = RAG ? part_lane(tid, wvol) : PartLane{tid, tid};
+    const int l = pl.l;
     const int t0 = chunk * tchunk;
     const int t1 = t0 + tchunk < Lt ? t0 + tchunk : Lt;
     // first site of this workgroup's part of slice t: cbase + t * bvol
@@ -297,8 +299,8 @@ __global__ void __launch_bounds__(kTmMaxBlock) k_dslash_tm(Geom g, const void *_
         else
             Link<LF>::template load<WD_NT_LINK || WD_NT_LINK_T>(gauge, 3, i, ut);
         // this wave's copy of the next slice has landed in LDS: the forward t
-        // hop reads only its own tile (the other waves' tiles are read after
-        // the barrier that ends the step)
+        // hop reads it at the lane's own place (the other waves' tiles are read
+        // after the barrier that ends the step)
         copy_landed<PREC>();
         const bool neg_tp = g.antiperiodic && t == Lt - 1 && (!HALO || halo.last);
         cx<R> c[12];
@@ -306,7 +308,7 @@ __global__ void __launch_bounds__(kTmMaxBlock) k_dslash_tm(Geom g, const void *_
             {
                 h2_t q[12];
                 float sc;
-                Spinor<WD_F16>::load_raw(nxt, l, q, sc);
+                Spinor<WD_F16>::load_raw(nxt, pl.place, q, sc);
                 h2_t h0[3], h1[3];
                 project_h2<3, SF>(q, h0, h1);
                 cx<float> w0[3], w1[3];
@@ -333,7 +335,7 @@ __global__ void __launch_bounds__(kTmMaxBlock) k_dslash_tm(Geom g, const void *_
         } else {
             {
                 cx<R> nx[12];
-                Spinor<PREC>::load(nxt, l, nx);
+                Spinor<PREC>::load(nxt, pl.place, nx);
                 hop_p<3, SF, false>(nx, ut, neg_tp, acc);
             }
             accumulate<3, SB>(cw0, cw1, acc);

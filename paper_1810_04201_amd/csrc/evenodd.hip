@@ -179,10 +179,12 @@ __global__ void __launch_bounds__(kTmMaxBlock) k_hop_half_tm(Geom g, const void 
     const int col = cc - chunk * ncols;
     const int Lt = g.L[3];
     const int tid = (int)threadIdx.x;
-    // entries of this workgroup's part; lanes past it repeat its last
+    // entries of this workgroup's part; lanes past it repeat its last (see
+    // k_dslash_tm)
     const int wvol = RAG && hvol - hp * w < w ? hvol - hp * w : w;
     const bool mine = !RAG || tid < wvol;
-    const int l = mine ? tid : wvol - 1;
+    const PartLane pl = RAG ? part_lane(tid, wvol) : PartLane{tid, tid};
+    const int l = pl.l;
     const int t0 = chunk * tchunk;
     const int t1 = t0 + tchunk < Lt ? t0 + tchunk : Lt;
     // first entry of this workgroup's part of half slice t: hbase + t * hvol
@@ -273,7 +275,7 @@ __global__ void __launch_bounds__(kTmMaxBlock) k_hop_half_tm(Geom g, const void 
         copy_landed<PREC>();
         {
             cx<R> nx[12];
-            Spinor<PREC>::load(nxt, l, nx);
+            Spinor<PREC>::load(nxt, pl.place, nx);
             hop_p<3, SF, false>(nx, ut, g.antiperiodic && t == Lt - 1, acc);
         }
         accumulate<3, SB>(cw0, cw1, acc);

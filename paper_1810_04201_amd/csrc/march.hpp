@@ -160,9 +160,9 @@ __device__ __forceinline__ void pin(cx<R> v[12]) {
     for (int k = 0; k < 12; ++k) asm volatile("" : "+v"(v[k].re), "+v"(v[k].im));
 }
 
-// Wait until this wave's outstanding copies have landed in LDS.  Only this
-// wave reads its tiles before the barrier that ends the step, so no barrier is
-// needed here: with one, the waves of a workgroup met twice per slice and
+// Wait until this wave's outstanding copies have landed in LDS.  Before the
+// barrier that ends the step a lane reads them at its own place alone (PartLane),
+// which its own wave filled, so no barrier is needed here: with one, the waves of a workgroup met twice per slice and
 // idled together (both forms timed in turn: the 12-source float32 solve on
 // 24^3 x 48 1.023 times as fast, a 48^3 x 12 slab pass 1.019; single launches at
 // 48^3 x 96 differ by less than their runs do).  Binary16 keeps the barrier: its plain stencil

@@ -436,6 +436,20 @@ inline PartShape part_shape(int n, int prec) {
     return p;
 }
 
+// Lane tid of a workgroup on a part of n sites (entries): the one it works on
+// (lanes past the part repeat its last), and the place of the LDS image that its
+// own wave copies that one to.  Until the barrier that ends a step a lane may read
+// the image being filled at `place` only: the site l of a lane past the part lies
+// in another wave's tile where the last part has fewer waves than its workgroup
+// (34^3 in float32: parts of 193 sites in four waves, the last of 192 in three).
+struct PartLane {
+    int l, place;
+};
+
+__host__ __device__ inline PartLane part_lane(int tid, int n) {
+    return PartLane{tid < n ? tid : n - 1, tid};
+}
+
 // On the smallest lattices parts of one wave: their launches last as long as one
 // workgroup's chain of loads and barriers, and more workgroups find idle CUs (8^4
 // CG iteration float64 30.4 -> 25.3 us, float32 26.6 -> 25.0; 12^4 34.9 against
