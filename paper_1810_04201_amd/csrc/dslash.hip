@@ -132,10 +132,11 @@ __global__ void __launch_bounds__(256) k_dslash(Geom g, const void *__restrict__
 // COUT: the output goes to a canonical float64 field (out.data) instead.
 // RAG: the brick slice is no whole number of tiles; parts of w sites that
 // start anywhere, the last one shorter (see PartShape; without HALO).  Such
-// lattices took one lane per site before: 30^3 x 60 float64 520 -> 319 us,
+// lattices took one lane per site before: 30^3 x 60 float64 520 -> 387 us,
 // float32 187 -> 148, binary16 95 -> 82, float64 CG iteration (with the fused
-// r update, which only this form has) 1584 -> 1033 us; 18^3 x 36 float64 69 ->
-// 43 us, CG iteration 212 -> 149.
+// r update, which only this form has) 1584 -> 1105 us; 18^3 x 36 float64 69 ->
+// 46 us, CG iteration 212 -> 148.  (Their float64 links have 18 reals: links12.
+// With 12 the stencil at 30^3 x 60 takes 320 us, the iteration 1000.)
 template <int PREC, bool DAG, bool RED, int GROUP, bool HALO = false, bool XR = false,
           int LF = PREC, bool COUT = false, bool RAG = false>
 __global__ void __launch_bounds__(kTmMaxBlock) k_dslash_tm(Geom g, const void *__restrict__ gauge,

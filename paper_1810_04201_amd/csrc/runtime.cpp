@@ -240,8 +240,7 @@ void dslash(wd_lattice *lat, const void *gauge, double kappa, int dagger, const 
             const FieldRef &out, const RedArgs *red, Gate gate, hipStream_t s) {
     // the kernels compute in - kappa' * (hops): the +kappa sign is kappa' = -kappa
     kappa = -lat->hop_sign * kappa;
-    // float64 on the lattice's own links: the 12-real form where it exists
-    const void *g12 = in.prec == WD_F64 && gauge == lat->gauge[WD_F64] ? lat->gauge12 : nullptr;
+    const void *g12 = links12(lat, in.prec, gauge);
     timed(kDslashNames[in.prec], s,
           [&] { launch_dslash(lat->g, gauge, kappa, dagger, in, out, red, gate, s, g12); });
 }
@@ -250,8 +249,8 @@ bool apply_direct(wd_lattice *lat, const void *gauge, double kappa, int prec, in
                   int nrhs, const double *in, double *out, hipStream_t s) {
     if (!apply_direct_ok(lat->g, prec, nrhs, in, out)) return false;
     timed(kDslashNames[prec], s, [&] {
-        launch_apply(lat->g, gauge, prec == WD_F64 ? lat->gauge12 : nullptr,
-                     -lat->hop_sign * kappa, prec, dagger, nrhs, in, out, s);
+        launch_apply(lat->g, gauge, links12(lat, prec, gauge), -lat->hop_sign * kappa, prec,
+                     dagger, nrhs, in, out, s);
     });
     return true;
 }
@@ -275,7 +274,7 @@ bool dslash_xr(wd_lattice *lat, const void *gauge, double kappa, int dagger, con
     if (!dslash_xr_supported(lat->g, in.prec, in.nrhs, red.partials_cap)) return false;
     kappa = -lat->hop_sign * kappa;
     static const char *names[3] = {"dslash_xr_f64", "dslash_xr_f32", "dslash_xr_f16"};
-    const void *g12 = in.prec == WD_F64 && gauge == lat->gauge[WD_F64] ? lat->gauge12 : nullptr;
+    const void *g12 = links12(lat, in.prec, gauge);
     bool ok = false;
     timed(names[in.prec], s, [&] {
         ok = launch_dslash_xr(lat->g, gauge, kappa, dagger, in, xr, red, gate, s, g12);

@@ -99,6 +99,16 @@ void hop_half_xr(wd_lattice *lat, void *const gh[2], int p, double kappa, double
 void dslash(wd_lattice *lat, const void *gauge, double kappa, int dagger, const FieldRef &in,
             const FieldRef &out, const RedArgs *red, Gate gate, hipStream_t s);
 
+// The F64-12 links that a full-lattice operator on `gauge` reads in its place
+// (nullptr: none): float64, the lattice's own links, bricks of whole tiles.  On
+// other bricks the 18 reals stay: row 2 of a link may be up to kSu3Tol off the one
+// that 12 reals rebuild, and a solve or an operator there has always used the
+// caller's (k_dslash_tm has the times of both).
+inline const void *links12(const wd_lattice *lat, int prec, const void *gauge) {
+    return prec == WD_F64 && gauge == lat->gauge[WD_F64] && tm_eligible(lat->g) ? lat->gauge12
+                                                                                 : nullptr;
+}
+
 // the operator on canonical spinors in one launch where there is such a form
 // (see launch_apply), with optional event timing; false: nothing launched
 bool apply_direct(wd_lattice *lat, const void *gauge, double kappa, int prec, int dagger,
