@@ -151,6 +151,8 @@ void launch_gauge_lo(const void *g64, void *glo, int form, int V, hipStream_t s)
         hipLaunchKernelGGL(k_gauge_lo<WD_F32>, gr, bs, 0, s, g64, glo, V);
     else if (form == WD_F16)
         hipLaunchKernelGGL(k_gauge_lo<WD_F16>, gr, bs, 0, s, g64, glo, V);
+    else if (form == kLinkF64R12)
+        hipLaunchKernelGGL(k_gauge_lo<kLinkF64R12>, gr, bs, 0, s, g64, glo, V);
     else if (form == kLinkF16R8)
         hipLaunchKernelGGL(k_gauge_lo<kLinkF16R8>, gr, bs, 0, s, g64, glo, V);
 }

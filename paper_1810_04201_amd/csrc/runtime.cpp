@@ -406,25 +406,16 @@ int wd_set_gauge(wd_lattice *lat, const double *U, void *stream) {
     }
     // float64 links also stored as 12 reals when every link is special
     // unitary to rounding (the marching stencil then reads 384 instead of
-    // 576 link bytes per site); WD_LINKS64_12=0 keeps 18 reals only.  The form
-    // is written along with the other, and dropped if the check then says no;
-    // without memory for it the lattice keeps 18 reals only.
+    // 576 link bytes per site); WD_LINKS64_12=0 keeps 18 reals only.  Where the
+    // lattice has the form it is written in the pass that packs and checks the
+    // links, and dropped if the check says no; else it is allocated once the
+    // check has said yes, so that links off the group never pay for it, and
+    // written from the 18 reals (24^3 x 48: 82 us, once in a lattice's life).
     const char *e12 = getenv("WD_LINKS64_12");
     const bool want12 = !(e12 && atoi(e12) == 0);
-    auto drop12 = [&] {
-        if (lat->gauge12) (void)hipFree(lat->gauge12);
-        lat->gauge12 = nullptr;
-    };
     lat->su3_dev = -1.0;
     unsigned long long hm = 0, *dm = nullptr;
     if (want12) {
-        if (!lat->gauge12) {
-            void *p = nullptr;
-            if (hipMalloc(&p, gauge_bytes(kLinkF64R12, lat->g.V)) == hipSuccess)
-                lat->gauge12 = p;
-            else
-                (void)hipGetLastError();
-        }
         dm = (unsigned long long *)((char *)lat->gauge[WD_F64] + bytes18);
         (void)hipMemsetAsync(dm, 0, sizeof(hm), s);
     }
@@ -439,9 +430,21 @@ int wd_set_gauge(wd_lattice *lat, const double *U, void *stream) {
         double dev;
         memcpy(&dev, &hm, sizeof(dev));
         lat->su3_dev = dev;
-        if (!(dev <= kSu3Tol)) drop12();
-    } else {
-        drop12();
+    }
+    bool pending = false;  // launches after the synchronisation
+    if (!(want12 && lat->su3_dev <= kSu3Tol)) {
+        if (lat->gauge12) (void)hipFree(lat->gauge12);
+        lat->gauge12 = nullptr;
+    } else if (!lat->gauge12) {
+        // without memory for it the lattice keeps 18 reals only
+        void *p = nullptr;
+        if (hipMalloc(&p, gauge_bytes(kLinkF64R12, lat->g.V)) == hipSuccess) {
+            lat->gauge12 = p;
+            launch_gauge_lo(lat->gauge[WD_F64], p, kLinkF64R12, lat->g.V, s);
+            pending = true;
+        } else {
+            (void)hipGetLastError();
+        }
     }
     // float64 halves whose form no longer matches are dropped (rebuilt on use)
     if (lat->gauge_eo[WD_F64][0] && lat->eo64_r12 != (lat->gauge12 != nullptr)) {
@@ -450,18 +453,17 @@ int wd_set_gauge(wd_lattice *lat, const double *U, void *stream) {
             lat->gauge_eo[WD_F64][q] = nullptr;
         }
     }
-    bool halves = false;
     for (int p = 0; p < 3; ++p)
         for (int q = 0; q < 2; ++q)
             if (lat->gauge_eo[p][q]) {
-                halves = true;
+                pending = true;
                 launch_gauge_split(lat->gauge[WD_F64], lat->gauge_eo[p][q],
                                    p == WD_F64 && lat->eo64_r12 ? kLinkF64R12
                                                                 : link_form(lat->g, p),
                                    q, lat->g, s);
             }
     WD_LAUNCH_CHECK();
-    if (halves) WD_HIP_CHECK(hipStreamSynchronize(s));
+    if (pending) WD_HIP_CHECK(hipStreamSynchronize(s));
     lat->has_gauge = true;
     return WD_OK;
 }

@@ -687,7 +687,7 @@ inline void choose_bricks(Geom &g) {
 // *maxbits must be set beforehand), and the F64-12 tiles where g12 is given
 void launch_ingest(const double *canon, void *g64, void *g12, unsigned long long *maxbits,
                    const Geom &g, hipStream_t s);
-// F64-18 tiles -> 12-real F32 or F16 tiles, or the 8-real F16 ones
+// F64-18 tiles -> 12-real F64, F32 or F16 tiles, or the 8-real F16 ones
 void launch_gauge_lo(const void *g64, void *glo, int form, int V, hipStream_t s);
 
 // canonical [rhs][V][12] float64 <-> field (format conversion + reorder)
