@@ -312,15 +312,22 @@ static March march_of(const Geom &g, int n, int nrhs) {
     m.p = geom_part(g, n, PREC);
     m.lds = 2 * slice_bytes<PREC>(m.p.threads);
     m.ok = m.lds + 64 <= cap;
-    m.tch = tm_chunk(g, nrhs * m.p.nsub);
+    // Binary16 with 12-real links rounds differently in the first slice of a chunk
+    // (its t hop is projected in float32) and in the others: on slices that are no
+    // whole tiles, where solves took one lane per site before they marched, the
+    // length is that of one rhs, so that a batch is its single solves bit for bit.
+    const bool as_single = PREC == WD_F16 && m.p.ragged && !g.f16_links8;
+    m.tch = tm_chunk(g, (as_single ? 1 : nrhs) * m.p.nsub);
     m.ncols = g.V / (g.L[3] * g.bvol);
     // chunks of one slice that do not all fit the chip at once, where chunks of
     // two do: those (each chunk pays for a slice before its first and one after
     // its last; 16^3 x 32 float64, one workgroup a CU: stencil 26.4 -> 24.9 us,
-    // CG iteration 85.0 -> 80.8)
+    // CG iteration 85.0 -> 80.8).  Not in binary16: the rule depends on nrhs, and a
+    // batch would no longer be its single calls.
     const int at_once = 256 * (int)(cap / m.lds);
     const int parts = m.ncols * m.p.nsub * nrhs;
-    if (m.tch == 1 && parts * g.L[3] > at_once && parts * ((g.L[3] + 1) / 2) <= at_once)
+    if (PREC != WD_F16 && m.tch == 1 && parts * g.L[3] > at_once &&
+        parts * ((g.L[3] + 1) / 2) <= at_once)
         m.tch = 2;
     // (not in binary16, whose steps are too short for the count: 24^3 x 48 38 us
     // at one and two slices, 40 at three, which it ranks first; nor from one
