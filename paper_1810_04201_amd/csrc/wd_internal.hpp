@@ -585,32 +585,33 @@ inline int largest_divisor_le(int n, int cap) {
 // parts of w consecutive local sites reads from outside each site's own part,
 // times 240 / (a b c): a direction the brick spans whole wraps inside it
 inline int part_faces(const int L[4], int a, int b, int c, int w) {
-    const int e[3] = {a, b, c};
+    // (without divisions: creating a lattice counts dozens of bricks, 18^3 300 us
+    // of host time with them, 82 so)
+    const int e[3] = {a, b, c}, step[3] = {1, a, a * b};
     long long out = 0;
-    for (int s = 0; s < a * b * c; ++s) {
-        const int q[3] = {s % a, (s / a) % b, s / (a * b)};
-        for (int d = 0; d < 3; ++d)
-            for (int step = -1; step <= 1; step += 2) {
-                int r[3] = {q[0], q[1], q[2]};
-                r[d] += step;
-                if (r[d] < 0 || r[d] >= e[d]) {
-                    if (e[d] < L[d]) {
-                        ++out;  // a brick face
-                        continue;
-                    }
-                    r[d] = (r[d] + e[d]) % e[d];
+    int s = 0, part = 0, q[3];  // the site, its part's first, its coordinates
+    for (q[2] = 0; q[2] < c; ++q[2])
+        for (q[1] = 0; q[1] < b; ++q[1])
+            for (q[0] = 0; q[0] < a; ++q[0], ++s) {
+                if (s == part + w) part = s;
+                for (int d = 0; d < 3; ++d) {
+                    const bool face = e[d] < L[d];
+                    const int wrap = (e[d] - 1) * step[d];
+                    const bool first = q[d] == 0, last = q[d] == e[d] - 1;
+                    const int m = first ? s + wrap : s - step[d];
+                    const int p = last ? s - wrap : s + step[d];
+                    out += (first && face) || m < part || m >= part + w;
+                    out += (last && face) || p < part || p >= part + w;
                 }
-                if ((r[0] + a * (r[1] + b * r[2])) / w != s / w) ++out;
             }
-    }
     return (int)(out * 240 / (a * b * c));
 }
 
 // Bricks where no extents give whole tiles: whole x rows, and the y and z
 // extents that lose the least to idle lanes and to neighbours outside the
 // parts, over the full slice and the half slice of one parity in float64 (the
-// neighbours counted on the full slice).  A unit of neighbours from outside costs about 7% (48^3 x 96: 2.0 of them 1.86
-// ms, none 1.61), idle lanes their share.
+// neighbours counted on the full slice).  A unit of neighbours from outside costs
+// about 7% (48^3 x 96: 2.0 of them 1.86 ms, none 1.61), idle lanes their share.
 inline void ragged_bricks(const Geom &g, int &bx, int &by, int &bz) {
     bx = g.L[0];
     by = largest_divisor_le(g.L[1], 8);
