@@ -244,8 +244,15 @@ int Solve::setup(hipStream_t stream, SlotRes *res) {
     // solves take an update every 10 to 15 iterations: the sum is least near
     // every 4 on large lattices (48^3 x 96 binary16 even-odd: 47 us of a 2.03
     // ms iteration with one after each) and every 8 on small ones; plain
-    // float64 needs only the one that ends it, once a chunk.
-    rel_every_ = !ctl_.mixed ? chunk_ : (n >= (1 << 20) ? 4 : 8);
+    // float64 needs only the one that ends it, once a chunk.  Where the caller
+    // asks for updates oftener than that (an rhs goes down by a factor of ten in
+    // about 12 iterations), a frozen rhs would wait longer than it iterates: after
+    // each iteration on large lattices, every 4 on small ones (4^4 float32 with
+    // reliable_max_iter 1: 10.2 ms at 8, 6.8 at 4; 24^3 x 48 binary16 120 and 113).
+    const bool large = n >= (1 << 20);
+    rel_every_ = !ctl_.mixed ? chunk_ : (large ? 4 : 8);
+    if (ctl_.mixed && (ctl_.max_inner < rel_every_ || -12.0 * std::log10(delta) < rel_every_))
+        rel_every_ = large ? 1 : 4;
     // chunks replayed from a captured HIP graph: cuts the host's launch work,
     // which bounds a server driving many small solves from one thread
     // (measured 113 -> 182 solves/s on 8^4 / 12^4 requests).  Needs a stream
