@@ -415,7 +415,7 @@ static void launch_prec(const Geom &g, const void *gauge, double kappa, int dagg
     // only when the caller's partial buffer holds them (it always does when
     // sized by reduce_partials_cap)
     March m = march_of<PREC>(g, g.bvol, in.nrhs);
-    if (PREC == WD_F16 && m.p.ragged && !red) m.ok = false;  // see launch_canon_out
+    if (m.p.ragged && !red && !ragged_marches<PREC>(g, in.nrhs)) m.ok = false;
     if (m.ok && (!red || (int64_t)tm_partials(g, m.p) * in.nrhs <= red->partials_cap)) {
         auto go = [&](auto lf, const void *links) {
             constexpr int F = decltype(lf)::value;
@@ -483,7 +483,7 @@ static void launch_canon_out(const Geom &g, const void *gauge, double kappa, Fie
     // always had (18^3 x 36, 2 rhs: 70.9 against 70.2 us); a solve's stencils
     // march.
     March m = march_of<PREC>(g, g.bvol, in.nrhs);
-    if (PREC == WD_F16 && m.p.ragged) m.ok = false;
+    if (m.p.ragged && !ragged_marches<PREC>(g, in.nrhs)) m.ok = false;
     if (m.ok) {
         launch_tm<PREC, DAG, false, false, LF, true>(m, g, gauge, in, out, kappa, RedArgs{}, none,
                                                      {}, s);

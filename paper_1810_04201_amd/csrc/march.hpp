@@ -341,4 +341,20 @@ static March march_of(const Geom &g, int n, int nrhs) {
     return m;
 }
 
+// Whether a plain application over slices that are no whole tiles marches: a
+// solve's reducing stencils always do, and plain ones give the same bits in both
+// forms.  Few sites over all rhs last as long as one workgroup's chain, in which
+// parts that leave lanes idle and chunks that read two slices more weigh most.
+// Float64, marching against one lane per site: 6^4 7.8 and 8.5 us; 14^4 12.6 and
+// 12.1, 6^3 x 20 x 12 12.6 and 11.6; 14^4 x 2 18.2 and 19.4, but 10^4 x 12, few sites
+// of each rhs, 25.9 and 22.4.  Float32: 14^4 8.4 and 7.0, 18^4 x 4 40.0 and 35.5,
+// 14^3 x 28 x 12 70 and 67; 18^3 x 36 22.5 and 24.2, 18^4 x 12 92 and 94, 18^3 x 36 x 12
+// 177 and 250.  Binary16: see launch_canon_out.
+template <int PREC>
+static bool ragged_marches(const Geom &g, int nrhs) {
+    const int64_t n = (int64_t)g.V * nrhs;
+    if (PREC == WD_F64) return n < 32768 || (n >= 65536 && g.V >= 16384);
+    return PREC == WD_F32 && (g.V >= 196608 || n >= (1 << 20));
+}
+
 }  // namespace wd
