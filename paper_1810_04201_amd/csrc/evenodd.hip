@@ -347,16 +347,22 @@ static bool eo_site_forced() {
 // 48^3 x 96 float64 half launches take 1.29-1.49 ms against 1.65-1.77 one
 // lane per site, float32 -2%, while binary16 (bound by its arithmetic) is
 // 3-8% slower marching and stays one lane per site.  Over half slices that are
-// no whole tiles float64 gains too (30^3 x 60 even-odd CG iteration 1046 ->
-// 1010 us, 22^3 x 44 Schur operator 237 -> 220), float32 does not (30^3 x 60,
-// the two launches of the operator: 114 + 133 us marching, 117 + 127 one lane
-// per site).
+// no whole tiles float32 does not gain (30^3 x 60, the two launches of the
+// operator: 114 + 133 us marching, 117 + 127 one lane per site).  Float64 does from
+// 12 time slices: with fewer, chunks that read two slices more and a last round of
+// few workgroups cost more than one lane per site does; and not between 32768 and
+// 200000 sites, which one round of one-lane workgroups holds.  48 iterations, one
+// lane per site against marching: 30^3 x 8 7.9 and 9.4 ms, x 12 12.8 and 12.0, x 20 22.8
+// and 18.6, x 60 61.6 and 56.8; 26^3 x 10 7.2 and 8.8, 26^4 18.9 and 16.1; 18^4 4.7 and
+// 5.3, 14^3 x 28 4.3 and 4.7; 10^3 x 20 3.4 and 3.0, 6^3 x 20 3.3 and 2.7.  (Not a rule
+// on the number of rhs: the sums of a batch are those of its single solves.)
 template <int PREC>
 static March eo_march(const Geom &g, int nrhs, bool red, int64_t partials_cap) {
     March m{};
     if (PREC == WD_F16 || eo_site_forced()) return m;
     m = march_of<PREC>(g, g.bvol / 2, nrhs);
-    if (PREC == WD_F32 && m.p.ragged) m.ok = false;
+    if (m.p.ragged && (PREC == WD_F32 || g.L[3] < 12 || (g.V >= 32768 && g.V < 200000)))
+        m.ok = false;
     if (red && m.ok) m.ok = (int64_t)tm_partials(g, m.p) * nrhs <= partials_cap;
     return m;
 }

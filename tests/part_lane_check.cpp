@@ -52,7 +52,7 @@ int main() {
     struct Case { int L[4], t[3], half, prec; };
     const Case cs[] = {{{34, 34, 4, 4}, {0, 0, 0}, 0, WD_F32},
                        {{386, 2, 2, 4}, {386, 1, 1}, 0, WD_F64},
-                       {{10, 14, 22, 4}, {10, 7, 11}, 1, WD_F64}};
+                       {{514, 2, 2, 12}, {514, 1, 1}, 1, WD_F64}};
     for (const Case &c : cs) {
         wd::Geom g{};
         g.V = 1;
