@@ -2,15 +2,16 @@
 a site (tests/part_lane_check.cpp counts them): 34^2 x 4 x 4 with its default brick
 in float32 (578 sites), slices of 386 sites in float64, half slices of 257.  Such a
 wave works on the part's last site too, which another wave's tile holds.
-Bars as for the other lattices: per site 1e-13 / 1e-5 against the oracle, solutions
-against the oracle's CG iterate after the same steps.
+Bars as for the other lattices: per site 1e-13 / 1e-5 against the oracle, the float64
+iterate after 16 steps 1e-11 against the oracle's, mixed solutions 1e-8 against the
+float64 one.
 """
 import numpy as np
 import pytest
 
 import synth
 from oracle import cg, evenodd, wilson
-from gpu_util import assert_same_count_parity, gauge, rel, site_rel_err
+from gpu_util import gauge, rel, site_rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -37,13 +38,14 @@ def _lattice(env, monkeypatch, dims, brick, seed):
     return lat, U
 
 
-@pytest.mark.parametrize("dims,brick", CASES)
+# (a plain float32 application marches from 196608 sites)
+@pytest.mark.parametrize("dims,brick", CASES + [((34, 34, 34, 6), None)])
 @pytest.mark.parametrize("prec", ["f64", "f32", "f16"])
 def test_operators(env, monkeypatch, dims, brick, prec):
     torch, dev, wd = env
     print(f"idle waves dims={dims} brick={brick} prec={prec}", flush=True)
     lat, U = _lattice(env, monkeypatch, dims, brick, 63)
-    n = 12  # (the operator on canonical spinors marches from 65536 sites)
+    n = -(-65536 // lat.volume)  # (the operator on canonical spinors marches then)
     src = synth.gaussian_sources(dims, list(range(90, 90 + n)))
     b = torch.from_numpy(src).to(dev)
     out = torch.full_like(b, float("nan"))
@@ -71,8 +73,9 @@ def test_operators(env, monkeypatch, dims, brick, prec):
     lat.close()
 
 
-@pytest.mark.parametrize("dims,brick", CASES)
-@pytest.mark.parametrize("even_odd", [False, True])
+# (the full slice of 514 sites leaves no wave idle)
+@pytest.mark.parametrize("dims,brick,even_odd", [CASES[0] + (False,), CASES[0] + (True,),
+                                                 CASES[1] + (False,), CASES[2] + (True,)])
 def test_solve(env, monkeypatch, dims, brick, even_odd):
     torch, dev, wd = env
     print(f"idle waves solve dims={dims} brick={brick} even_odd={even_odd}", flush=True)
@@ -80,16 +83,18 @@ def test_solve(env, monkeypatch, dims, brick, even_odd):
     src = synth.gaussian_spinor(dims, 95)
     b = torch.from_numpy(src).to(dev)
     x = torch.zeros_like(b)
-    rc, info = lat.solve(b, x, 0.12, even_odd=even_odd)
-    assert rc == wd.WD_OK, info
-    n = info[0]["iters"]
+    n = 16
+    rc, info = lat.solve(b, x, 0.12, tol=1e-14, max_iter=n, even_odd=even_odd)
+    assert rc == wd.WD_ERR_NOCONV and info[0]["iters"] == n
     if even_odd:
         want, _, _ = evenodd.solve(U, src, dims, 0.12, tol=1e-300, max_iter=n)
     else:
         want, _, _ = cg.cgnr(lambda v: wilson.apply_D(U, v, dims, 0.12),
                              lambda v: wilson.apply_Ddag(U, v, dims, 0.12), src, tol=1e-300,
                              max_iter=n)
-    assert_same_count_parity(x.cpu().numpy(), want)
+    assert rel(x.cpu().numpy(), want) <= 1e-11
+    rc, info = lat.solve(b, x, 0.12, even_odd=even_odd)
+    assert rc == wd.WD_OK, info
     for prec in ("f32", "f16"):
         lo = torch.zeros_like(b)
         rc, info = lat.solve(b, lo, 0.12, prec=prec, even_odd=even_odd)
