@@ -326,15 +326,26 @@ static March march_of(const Geom &g, int n, int nrhs) {
     // batch would no longer be its single calls.
     const int at_once = 256 * (int)(cap / m.lds);
     const int parts = m.ncols * m.p.nsub * nrhs;
-    if (PREC != WD_F16 && m.tch == 1 && parts * g.L[3] > at_once &&
-        parts * ((g.L[3] + 1) / 2) <= at_once)
+    const int wgs = wgs_at_once(PREC, m.p.threads, m.lds);
+    // Where two float64 workgroups share a CU, no length whose workgroups are under
+    // four fifths of what fits at once: some CUs have one of them and others two,
+    // and the launch lasts as long as two (24 x 8 x 8 x 24 with 3 rhs 22.0 us in
+    // chunks of one slice, 288 of 512 workgroups in chunks of two 26.0; 12^3 x 36 with
+    // 2 rhs 24.1 and 26.6; but 24^3 x 4 with 3 rhs, 432 of 512, 34.0 and 31.2).
+    auto uneven = [&](int c) {
+        return PREC == WD_F64 && wgs == 512 &&
+               5 * parts * ((g.L[3] + c - 1) / c) < 4 * wgs;
+    };
+    if (PREC != WD_F16 && env_chunk() <= 0 && m.tch == 1 && parts * g.L[3] > at_once &&
+        parts * ((g.L[3] + 1) / 2) <= at_once && !uneven(2))
         m.tch = 2;
     // (not in binary16, whose steps are too short for the count: 24^3 x 48 38 us
     // at one and two slices, 40 at three, which it ranks first; nor from one
     // slice in float32, the same: 18^3 x 36 x 2 38 us, 40 at three)
-    if ((PREC == WD_F64 || (PREC == WD_F32 && m.tch > 1)) && env_chunk() <= 0)
-        m.tch = balanced_chunk(g.L[3], parts, wgs_at_once(PREC, m.p.threads, m.lds), m.tch,
-                               chunk_gain(PREC, nrhs));
+    if ((PREC == WD_F64 || (PREC == WD_F32 && m.tch > 1)) && env_chunk() <= 0) {
+        const int c = balanced_chunk(g.L[3], parts, wgs, m.tch, chunk_gain(PREC, nrhs));
+        if (!uneven(c)) m.tch = c;
+    }
     m.chunks = (g.L[3] + m.tch - 1) / m.tch;
     m.grid = dim3(m.ncols * m.chunks * m.p.nsub * nrhs);
     m.bs = dim3(m.p.threads);
