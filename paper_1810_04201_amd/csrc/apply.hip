@@ -6,9 +6,10 @@
 // are the resident internal forms.
 //
 // Bound by memory: links and two spinors per site, 768 bytes in float64 where
-// the three passes moved 1536.  48^3 x 96 3.60 -> 2.02 ms (4.0 TB/s of those
-// 768 bytes), 24^3 x 48 238 -> 131 us, 18^3 x 36, whose bricks are no whole
-// tiles, 117 -> 48 us, 8^4 25 -> 7.5 us a call.  Float32 takes this form on
+// the three passes moved 1536.  48^3 x 96 3.52 -> 1.94 ms (4.2 TB/s of those
+// 768 bytes), 24^3 x 48 237 -> 118 us, 16^3 x 32 52.8 -> 26.8; 18^3 x 36, whose
+// bricks are no whole tiles and whose links have 18 reals, 115 -> 47 us; 8^4 33 ->
+// 8.2 us a call.  Float32 takes this form on
 // small lattices only: its image would be float64 too, and reading float64
 // faces costs it more than the import (24^3 x 48, 12 rhs: 1.64 ms against
 // 1.18 for import and launch_dslash_canon).
@@ -262,7 +263,7 @@ __global__ void __launch_bounds__(kApplyPart, 2)
         // after each pair of hops the sum is made opaque: the compiler
         // otherwise moves the arithmetic of all hops behind the loads of the
         // last one and spills.  Pairs against single hops: 48^3 x 96 2.02
-        // against 2.04 ms, 18^3 x 36 48.5 against 50.5 us.
+        // against 2.04 ms, 18^3 x 36 (12-real links) 48.5 against 50.5 us.
         auto fence = [&] {
 #pragma unroll
             for (int k = 0; k < 12; ++k) asm volatile("" : "+v"(acc[k].re), "+v"(acc[k].im));

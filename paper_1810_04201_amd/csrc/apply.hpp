@@ -8,8 +8,8 @@ namespace wd {
 constexpr int kApplySiteBlock = 64;
 // sites per marching workgroup, at most: two workgroups of 192, with two 39
 // KiB images each, share a CU.  384 (one workgroup per CU) measured 2.01
-// against 2.04 ms at 48^3 x 96 but 371 against 339 us at 30^3 x 60, whose
-// bricks fill parts of 192 better.
+// against 2.04 ms at 48^3 x 96 but 371 against 339 us at 30^3 x 60 (12-real
+// links), whose bricks fill parts of 192 better.
 constexpr int kApplyPart = 192;
 
 // The marching form, else one lane per site.  The line: 12^3 x 24 (41472

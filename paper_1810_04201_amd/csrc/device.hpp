@@ -649,9 +649,9 @@ struct Link<kLinkF16R8> {
 //
 // Deterministic and split in two launches: every block of the producing
 // kernel reduces its contribution (one rhs per block: a fixed butterfly
-// inside each wave, then the waves in order) and writes one partial; a
-// one-block finalize kernel then sums the partials of each rhs in a fixed
-// order and updates the solver state.  The kernel boundary orders the
+// inside each wave, then the waves in order) and writes one partial; a finalize
+// kernel of a block per rhs, or the kernel that needs the sum, then sums the
+// partials in a fixed order and steps the solver state.  The kernel boundary orders the
 // two phases, so no device-scope fence (an L2 write-back on this chip) is
 // issued per block.  Results are bitwise reproducible for a launch shape.
 
@@ -791,7 +791,7 @@ __device__ inline void reduce_block(double v, double *partials, size_t idx) {
 // lattices the kernel that needs the sum (Cons): its workgroups all sum the same
 // few partials, so that an iteration is three launches instead of five.  The
 // loads are issued first (defer_load) and used after the kernel's own first
-// loads are on their way (defer_step): waited for at once they cost the two
+// loads are on their way (defer_sum): waited for at once they cost the two
 // kernels of a 16^3 x 32 iteration 15 us, more than the two launches of
 // k_finalize (9.3 us and the gaps).
 

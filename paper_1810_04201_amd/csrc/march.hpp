@@ -266,7 +266,7 @@ static int env_chunk() {
 }
 static int tm_chunk(const Geom &g, int nrhs) { return tm_chunk_len(g, nrhs, env_chunk()); }
 
-// WD_SITE_KERNEL=1 forces the one-lane-per-site stencil everywhere (tuning)
+// WD_SITE_KERNEL=1 forces the one-lane-per-site stencils on internal fields (tuning)
 static const bool g_force_site_kernel = [] {
     const char *e = getenv("WD_SITE_KERNEL");
     return e && atoi(e) != 0;

@@ -222,8 +222,8 @@ inline size_t field_data_bytes(int prec, int V, int nrhs) {
 // ------------------------------------------------------------------ solver state
 //
 // One RhsState per right-hand side lives in device memory.  The kernels read
-// alpha/beta/active from it and the reduction finaliser (run by the last
-// block of a reducing kernel) writes it, so a CG iteration needs no host
+// alpha/beta/active from it and the end of a reduction (k_finalize, or the
+// kernel that needs the sum: Cons) writes it, so a CG iteration needs no host
 // round trip.  A frozen rhs (active == 0) is skipped by every kernel, which
 // makes iterations enqueued after convergence exact no-ops.
 struct RhsState {
@@ -353,11 +353,10 @@ inline int blocks_for(int64_t n, int bs) { return (int)((n + bs - 1) / bs); }
 // Field kernels run a grid of site_blocks(V) x nrhs workgroups of kSiteBlock
 // lanes (one lane per site of one rhs) and a reducing one writes a partial
 // per workgroup, at index site block * nrhs + rhs.  The time-marching stencil
-// runs one workgroup of w = tm_wvol lanes per brick column, chunk of time
-// slices, part h of the bvol / w parts of a brick slice, and rhs, and writes
-// a partial per part of a brick slice, at index
-// ((column * Lt + t) * (bvol / w) + h) * nrhs + rhs.  The solver sizes its
-// partial buffer from these same functions.
+// runs one workgroup per brick column, chunk of time slices, part h of the nsub
+// parts of a brick slice (PartShape), and rhs, and writes a partial per part of a
+// brick slice, at index ((column * Lt + t) * nsub + h) * nrhs + rhs.  The solver
+// sizes its partial buffer from these same functions.
 
 constexpr int kSiteBlock = 256;
 
@@ -402,9 +401,10 @@ inline int part_sites(int n, int prec) {
 
 inline int tm_wvol(const Geom &g, int prec) { return part_sites(g.bvol, prec); }
 
-// entries per workgroup of the marching half-field stencil: the same rule
+// entries per workgroup of the marching half-field stencil by the same rule
 // on a half slice (bvol / 2 entries of one parity); 0 where a half slice is
-// not whole tiles
+// not whole tiles.  (Launches go by eo_part, which takes one wave on the smallest
+// lattices; the host check of the entry mapping goes by this.)
 inline int eo_wvol(const Geom &g, int prec) {
     const int hvol = g.bvol / 2;
     if (hvol % 64) return 0;
@@ -494,7 +494,7 @@ inline int wgs_at_once(int prec, int threads, size_t lds) {
 
 // The least gain by balanced_chunk's count for which it changes the length, both
 // sides of the line in us: one rhs in float64, D on canonical spinors at 32^3 x 64 (5% by
-// the count) 406 -> 362, the stencil at 30^3 x 60 (7%) 321 -> 319; in float32
+// the count) 406 -> 362, the stencil at 30^3 x 60 (7%, 12-real links) 321 -> 319; in float32
 // 24^3 x 48 (10%) 59 -> 56.  Several rhs, which share their links through L2,
 // gain less: 16^3 x 32 x 12 float32 (15%) 102 -> 95, but 24^3 x 48 x 2 float64 (9%)
 // 211 -> 215, 32^3 x 64 x 4 float32 (5%) 582 -> 590.
@@ -538,8 +538,8 @@ inline int balanced_chunk(int Lt, int64_t parts, int at_once, int c0, double gai
     return least < (1.0 - gain) * start ? best : c0;
 }
 
-// column chunks of the time-marching stencil (each runs bvol / w
-// workgroups per rhs)
+// column chunks of the time-marching stencil (each runs a workgroup per part and
+// rhs); for the host check that chunks tile the time extent
 inline int tm_blocks(const Geom &g, int chunk_len) {
     const int ncols = g.V / (g.L[3] * g.bvol);
     return ncols * ((g.L[3] + chunk_len - 1) / chunk_len);
