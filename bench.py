@@ -63,7 +63,8 @@ SPINOR_BYTES = {"f64": 192, "f32": 96, "f16": 52}
 HBM_PEAK_GBS = 8000.0
 METRIC = "dslash GFLOP/s & HBM GB/s; CG time-to-1e-10 residual, mixed vs FP64"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "dslash_traffic_48x48x48x96.json")
-KERNEL_SOURCES = ["dslash.hip", "march.hpp", "hops.hpp", "device.hpp", "wd_internal.hpp"]
+KERNEL_SOURCES = ["dslash.hip", "evenodd.hip", "march.hpp", "hops.hpp", "device.hpp",
+                  "wd_internal.hpp"]
 
 
 def log(*a):
